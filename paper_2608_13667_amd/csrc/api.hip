@@ -24,9 +24,9 @@ struct fka_plan {
     int32_t n_branches = 0;    // instruction prefill plan: branches
     int32_t prefill_groups = 1; // instruction prefill plan: units per block
     // instruction prefill on the tiled kernel (head_dim 128): 32-row units per KV head, blocks of
-    // eight units, prefix ranges, prefix tiles of 64 keys, tiles of balance left to the suffix keys
+    // eight units, key ranges, whole prefix tiles of 64 keys
     bool prefill_tiles = false;
-    int32_t tile_units = 0, tile_unit_groups = 0, tile_ranges = 0, tile_prefix = 0, tile_reserve = 0;
+    int32_t tile_units = 0, tile_unit_groups = 0, tile_ranges = 0, tile_prefix = 0;
     int32_t max_suffix_len = 0;
     // contiguous
     int32_t prefix_len = 0, suffix_cap = 0;
@@ -412,7 +412,6 @@ fka_status run_prefill(const fka_plan *p, const fka::AttnArgs &a, float *out, fl
         t.unit_groups = p->tile_unit_groups;
         t.ranges = p->tile_ranges;
         t.prefix_tiles = p->tile_prefix;
-        t.tail_reserve = p->tile_reserve;
         t.scale_log2 = p->scale * 1.4426950408889634f;
         e = fka::launch_prefill_tiles(t, p->n_blocks, s);
         if (e != hipSuccess) return hip_fail(e, "prefill kernel launch");
@@ -518,17 +517,13 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
     const int tile_rows = fka::prefill_tiles_unit_rows(), tile_waves = fka::prefill_tiles_waves();
     if (p->d == 128 && S * G >= (int64_t)tile_waves * tile_rows) {
         // The tiled kernel: units of 32 consecutive rows of a KV head, eight per block (one per
-        // wave) over one range of whole 64-key prefix tiles; R ranges fill the device, and the
-        // last range's share is shortened by the keys it also reads per wave: the prefix's last
-        // Lp mod 64 and the suffix keys, taken as the instruction itself (the branches' suffixes
-        // are empty at the fork); a 32-key tile, read without prefetch, is counted as one 64-key
-        // prefix tile.
+        // wave) over one of R ranges of the keys, R such that the blocks fill the device.
         const int per_cu = fka::prefill_tiles_blocks_per_cu(lay.paged);
         if (per_cu <= 0) return bail(fail(FKA_ERR_HIP, "occupancy query of the prefill kernel failed"));
         const int64_t rows_head = S * G;
         const int32_t U = (int32_t)ceil_div(rows_head, tile_rows);
         const int32_t UG = ceil_div(U, tile_waves);
-        const int32_t PT = Lp / 64;  // whole tiles; the last range reads the rest per wave
+        const int32_t PT = Lp / 64;  // whole tiles; the rest goes with the suffix keys
         const int64_t base = (int64_t)p->Hkv * UG;
         const int64_t want = blocks > 0 ? blocks : (int64_t)cus * per_cu;
         int64_t R = std::max<int64_t>(1, want / base);
@@ -541,7 +536,6 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
         p->tile_unit_groups = UG;
         p->tile_ranges = (int32_t)R;
         p->tile_prefix = PT;
-        p->tile_reserve = (int32_t)std::min<int64_t>(ceil_div(n, 32) + (Lp % 64 != 0), PT / (2 * R));
         for (int32_t u = 0; u < U; ++u) {
             fka::UnitRec r{};
             r.seq0 = (int32_t)(((int64_t)u * tile_rows) / G);

@@ -236,10 +236,10 @@ struct ScatterArgs {
 // are cut into units of 32 (row i: query head g G + i mod G of virtual sequence i / G, where
 // sequence s = b n + t is instruction token t of branch b); block vb takes KV head vb mod Hkv,
 // unit group k = (vb / Hkv) mod unit_groups (units [floor(k U / UG), floor((k + 1) U / UG)), at
-// most eight, one per wave) and prefix range
-// vb / (Hkv unit_groups) of `ranges`, range r covering prefix tiles (64 keys) [floor(r T / R),
-// floor((r + 1) T / R)) of T = prefix_tiles + tail_reserve, clamped to the whole tiles; the last
-// range also reads the prefix keys past them (Lp mod 64) and the suffix keys.  Part r of output row (s, h) is written at
+// most eight, one per wave) and range r = vb / (Hkv unit_groups) of `ranges`: of the T tiles of 64
+// keys its rows read -- the prefix's whole tiles, then its last Lp mod 64 keys and the suffix keys
+// in groups of eight, counted on the device from the suffix lengths -- those in [floor(r T / R),
+// floor((r + 1) T / R)).  Part r of output row (s, h) is written at
 // part_o[(r S Hq + s Hq + h) d] and part_lse[r S Hq + s Hq + h].
 struct PrefillArgs {
     const uint16_t *q;                    // [S][Hq][d]
@@ -260,7 +260,6 @@ struct PrefillArgs {
     int32_t unit_groups;   // ceil(n_units / 8)
     int32_t ranges;        // R
     int32_t prefix_tiles;  // floor(Lp / 64): whole 64-key tiles
-    int32_t tail_reserve;  // tiles of the balance given to the last range's per-wave keys
     float scale_log2;      // softmax scale * log2(e)
 };
 

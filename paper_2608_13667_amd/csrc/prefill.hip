@@ -12,8 +12,8 @@
 // Work: the rows of KV head g are cut into units of 32 consecutive rows (row i of the head is
 // query head g G + i mod G of sequence i / G), one unit per wave.  A block of eight waves takes
 // up to eight units of one KV head (the units spread evenly over the blocks of a range) over one
-// range of prefix tiles (64 keys each); the prefix is split into R ranges so that the blocks fill
-// the device, and the block of the last range also takes the suffix keys.  Each wave writes one normalised partial (o, lse) per row for its range, and
+// range of key tiles (64 keys each); the keys are split into R ranges so that the blocks fill
+// the device.  Each wave writes one normalised partial (o, lse) per row for its range, and
 // the merge kernel combines a row's R partials (its explicit mode).
 //   * K and V tiles go from HBM (or L2: the blocks of one KV head and range run on one XCD when
 //     the KV heads are a multiple of 8 apart in the grid order) into LDS by DMA
@@ -26,14 +26,25 @@
 //   * S^T = K Q^T and O^T += V^T P^T run on v_mfma_f32_16x16x32_bf16 with keys on M, so each
 //     lane owns two query rows of the online softmax (rows l16 and 16 + l16 of the unit) and
 //     16 keys of each per tile; P enters the second product as two bf16 terms (hi + lo);
-//   * K is read from LDS in the A-operand layout (16-byte chunks xor-swizzled by row, so a
-//     16-lane read touches every bank once), V transposed with ds_read_b64_tr_b16;
-//   * the running maximum moves only when a score exceeds it by more than 2^8;
-//   * suffix keys (the instruction and any suffix before it) are read per wave after the prefix
-//     range, 32 keys at a time, K straight into registers and V through a wave-private LDS
-//     area, with each row masked to its own branch and causal limit.  A non-finite value there
-//     is replaced by zero for the product and the rows that read its key are made NaN, so that
-//     it reaches no row of another branch or of an earlier token.
+//   * K is read from LDS in the A-operand layout, V transposed with ds_read_b64_tr_b16, both
+//     xor-swizzled by row so that a read touches every bank once, and both two groups of operands
+//     ahead of the products;
+//   * a row's reference of the exponentials moves only when its p have grown past a limit;
+//   * the keys past the prefix's whole tiles -- its last Lp mod 64, then the suffix keys of every
+//     branch the block's rows belong to -- form tiles of eight 8-key groups, each group of one branch,
+//     which go through the same buffers; each row is masked to its own branch and causal limit.
+//     The ranges share these tiles like the others (their number follows from the suffix lengths
+//     on the device).  A non-finite value there is replaced by zero for the product and the rows
+//     that read its key are made NaN, so that it reaches no row of another branch or of an earlier
+//     token.
+// What bounds it: beside a wave that issues matrix products at full rate the other wave of the SIMD
+// gets one vector issue per 8.7 cycles (two per product), so a step cannot be shorter than 2 x 96
+// products (3340 cycles) nor than the two softmaxes' ~225 issue slots each (3900); it takes 3940
+// (124 steps, 32k prefix, 64 tokens x 5 branches, 40 / 8 heads), where the chip's power limit holds
+// the clock at 2.2 of 2.4 GHz.  With the operands read in bursts that were waited for whole, a
+// maximum per tile and the keys past the whole tiles read wave by wave, one round trip to memory per
+// 32 keys (25000 cycles in the last range), it took 4920: 292 us a call against 268 now, 233
+// against 215 at 256 tokens x 1 sequence over 33.8k keys, 74.5 against 70 at 16 x 5 over 23k.
 #include <type_traits>
 #include <utility>
 
@@ -49,25 +60,14 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(4))) const int32_t const_i32;
 
-constexpr int HD = 128;            // head dimension of this kernel
-constexpr int ROWB = HD * 2;       // bytes per key row
-constexpr int NC = HD / 32;        // k-steps of the q.k product
-constexpr int NE = HD / 16;        // 16-wide d tiles of the output
 constexpr int KT = 64;             // keys per prefix tile
 constexpr int NW = 8;              // waves per block (two per SIMD)
 constexpr int STAGES = 4;          // prefix tile buffers: two read, two loading
-constexpr int KBYTES = KT * ROWB;  // 16 KiB of K (or V) per tile
-constexpr int K_LDS = 0;           // K buffers at [0, 64 KiB)
-constexpr int V_LDS = STAGES * KBYTES;  // V buffers at [64, 128 KiB)
-constexpr int LDS_BYTES = 2 * STAGES * KBYTES;
-constexpr int ST = 32;             // keys per suffix tile
-constexpr int SUF_LDS = ST * ROWB; // per-wave V area for a suffix tile (8 KiB), reusing the stages
+constexpr int GRP = 8;             // keys per group of a tail tile (what one wave loads of a tile)
 constexpr float kLn2 = 0.693147180559945309f;
-constexpr float kRescaleGap = 8.0f;  // log2 units
+constexpr float kRescaleLimit = 256.f;  // a lane's sum of p over a tile past which its rows' references move
 
-static_assert(NW * SUF_LDS <= LDS_BYTES, "suffix areas fit the stage buffers");
 static_assert(STAGES == 4, "the tile loop is unrolled over its four buffers");
-static_assert((STAGES - 1) * KBYTES + 3 * 16 * ROWB < 65536, "LDS offsets fit the immediate field");
 
 __device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
 {
@@ -125,14 +125,18 @@ __device__ inline float max2(float a, float b)
     return r;
 }
 
-// Reductions over lanes l, l ^ 16, l ^ 32, l ^ 48 (the four lanes holding one query row).  The
-// maximum's inputs are maxima of matrix-core results (no signalling NaN).
-__device__ inline float max_over_rows(float x)
+// Maxima of two rows, x0 and x1, over lanes l, l ^ 16, l ^ 32, l ^ 48 (the four lanes holding a query
+// row): the first exchange leaves row 0 in the lower half of the wave and row 1 in the upper, the
+// last spreads both.  The inputs are maxima of matrix-core results (no signalling NaN).
+__device__ inline void max_over_rows2(float &x0, float &x1)
 {
-    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+    const float x = max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
     const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return max2(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    const float y = max2(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    x0 = __uint_as_float(c[0]);
+    x1 = __uint_as_float(c[1]);
 }
 
 __device__ inline float sum_over_rows(float x)
@@ -154,6 +158,15 @@ __device__ inline u32x4 ds_read_b128_at(uint32_t addr)
     return r;
 }
 
+template <int OFFSET>
+__device__ inline uint64_t ds_read_b64_at(uint32_t addr)
+{
+    static_assert(OFFSET >= 0 && OFFSET < 65536, "ds offset field");
+    uint64_t r;
+    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFFSET) : "memory");
+    return r;
+}
+
 // ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives element i % 4 of the rows
 // addressed by lanes i / 4, 4 + i / 4, 8 + i / 4 and 12 + i / 4 (the transpose of a 16 x 4 block).
 typedef long vtr_t;
@@ -167,6 +180,20 @@ __device__ inline vtr_t ds_read_tr16(uint32_t addr)
 }
 
 __device__ inline void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Waits until at most N LDS reads are outstanding.
+template <int N>
+__device__ inline void lds_wait_to()
+{
+    static_assert(N >= 0 && N < 16, "lgkmcnt range");
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(N) : "memory");
+}
+
+// Every lane writes the same 8 bytes at one address (valid for the block after a barrier that waits for LDS).
+__device__ inline void ds_write_b64(uint32_t addr, uint64_t x)
+{
+    asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(x) : "memory");
+}
 
 // Block barrier after this wave's LDS reads have returned (global loads stay in flight).
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -228,6 +255,8 @@ __device__ inline bf16x8 join_tr16(vtr_t lo, vtr_t hi)
 
 // Splits p into hi + lo, both bf16: hi keeps the top 16 bits of p, lo is the rest rounded.
 // Packs the values of two key groups (four each) into the B operand of one p.v product.
+// (v_dot2_f32_bf16 over the packed hi terms gives p - hi in one instruction instead of two, but
+// measured 5% more cycles per tile.)
 __device__ inline void split_p(const float (&p)[8], bf16x8 &hi, bf16x8 &lo)
 {
     uint32_t hw[4];
@@ -241,10 +270,65 @@ __device__ inline void split_p(const float (&p)[8], bf16x8 &hi, bf16x8 &lo)
     for (int i = 0; i < 8; ++i) lo[i] = (__bf16)r[i];
 }
 
-template <bool PAGED>
+// A matrix phase works in groups of products: NV groups of p.v (two d tiles of a 32-key k-step: 8
+// products, 128 cycles), then NK of q.k (one 16-key score tile: 8 products at d = 128), with VR or KR LDS
+// reads each.  Operands are read two groups ahead (three groups in flight: the counter of LDS reads
+// holds 15), so that only the first group waits for LDS, also while a tile's loads are being written there: reads return in order, so
+// "at most N outstanding", N the reads of the groups requested behind it, means a group's are in.
+template <int NV, int NK, int VR, int KR>
+struct MatrixPlan {
+    static constexpr int AHEAD = 2;
+    static_assert((AHEAD + 1) * (VR > KR ? VR : KR) <= 15, "reads in flight");
+    // the group before which group j is requested, in a phase that starts at group `first`
+    static constexpr int due(int j, int first)
+    {
+        const int d = j - AHEAD;
+        return d > first ? d : first;
+    }
+    static constexpr int behind(int q, int first)
+    {
+        int n = 0;
+        for (int j = q + 1; j < NV + NK; ++j)
+            if (due(j, first) <= q) n += j < NV ? VR : KR;
+        return n;
+    }
+};
+
+// The kernel's lambdas are inlined whatever their size: a call would keep what they capture in
+// scratch memory.
+#define INLINE __attribute__((always_inline))
+
+// Layout of the 16x16x32 products: the output tile holds 16 keys (or 16 d) x 16 query rows; lane
+// (q4, l16) = (l / 16, l mod 16) owns column l16 and rows 4 q4 + j (register j).  (The 32x32x16 op
+// needs fewer cross-lane steps, but the same products take half as much energy again there: at the
+// power limit, registers only, 1370 TFLOP/s against 2000; here the clock fell from 2.4 to 2.0 GHz
+// and the call took as long.)
+template <int HD, bool PAGED>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void prefill_tiles_kernel(PrefillArgs a)
 {
+    constexpr int ROWB = HD * 2;            // bytes per key row
+    constexpr int CPR = HD / 8;             // 16-byte chunks per key row
+    constexpr int NC = HD / 32;             // k-steps of the q.k product
+    constexpr int NE = HD / 16;             // 16-wide d tiles of the output
+    constexpr int MT = KT / 16;             // 16-key score tiles per prefix tile
+    constexpr int KS = KT / 32;             // 32-key k-steps of p.v per prefix tile
+    constexpr int EG = 2;                   // d tiles per group of V operands
+    constexpr int KBYTES = KT * ROWB;       // K (or V) of one prefix tile
+    constexpr int V_LDS = STAGES * KBYTES;  // K buffers first, then V buffers
+    constexpr int LDS_BYTES = 2 * STAGES * KBYTES;
+    constexpr int RPI = 64 / CPR;           // key rows one DMA instruction moves
+    constexpr int DMAS = 8 / RPI;           // DMA instructions for a wave's 8 rows of K (or V)
+    static_assert(NW * GRP == KT, "one group of a tile per wave");
+    static_assert((STAGES - 1) * KBYTES + (KT - 16) * ROWB < 65536, "LDS offsets fit the immediate field");
+    // LDS chunk position of chunk c of row r: c ^ swz(r).  K is read 16 consecutive rows at one
+    // chunk (ds_read_b128), V 8 consecutive rows at 2 consecutive chunks (the transposed read, half
+    // a wave): both then touch every 16-byte slot of the 256-byte bank line once.
+    auto swz_k = [](int r) { return CPR == 16 ? (r & 15) : ((r >> 1) & 7); };
+    auto swz_v = [](int r) { return CPR == 16 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); };
+
     __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
+    // per tile buffer, the groups of a tail tile: branch and last key (see issue_tail)
+    __shared__ __attribute__((aligned(16))) int2 s_grp[STAGES][NW];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, l16 = lane & 15, q4 = lane >> 4;
@@ -265,37 +349,97 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const bool active = u < mul_div(ug + 1, a.n_units, a.unit_groups);
     const int R = a.ranges;
     const int PT = a.prefix_tiles;
-    const int total = PT + a.tail_reserve;
-    const int t0 = min(PT, mul_div(r, total, R)), t1 = (r == R - 1) ? PT : min(PT, mul_div(r + 1, total, R));
-    const int ntile = t1 - t0;
 
-    // ---- per-lane constants
+    // ---- the block's keys: the prefix's whole tiles, then the tail -- the prefix's last Lp mod 64 keys
+    // (every row reads them) and the suffix keys of the branches its rows belong to, each branch up
+    // to the last key any of the block's rows reads -- in groups of eight keys, eight groups to a tile.
+    // The ranges share both: range r takes the prefix's tiles [s0, s0 + nmain) (known from the plan, so
+    // their loads do not wait for the suffix lengths) and tail tiles [tail_t0, + its share), the
+    // first spare tail tile going to the first range without a spare prefix tile.
+    const int pre_each = PT / R, pre_more = PT - pre_each * R;
+    const int s0 = r * pre_each + min(r, pre_more), nmain = pre_each + (r < pre_more ? 1 : 0);
+
     // DMA: this wave moves tile rows [8 wave, 8 wave + 8): instruction ii writes rows
-    // 8 wave + 4 ii + lane / 16, lane's LDS chunk position lane % 16, which holds the row's
-    // global chunk position ^ swizzle(row) (K: row mod 16, V: 2 row mod 16)
-    uint32_t koff[2], voff[2];
+    // 8 wave + RPI ii + lane / CPR, lane's LDS chunk position lane % CPR, which holds the row's
+    // global chunk position ^ swizzle(row)
+    uint32_t koff[DMAS], voff[DMAS];
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii) {
-        const int tl = 4 * ii + (lane >> 4), pos = lane & 15, T = 8 * wave + tl;
-        koff[ii] = tl * ROWB + 16 * (pos ^ (T & 15));
-        voff[ii] = tl * ROWB + 16 * (pos ^ ((2 * T) & 15));
+    for (int ii = 0; ii < DMAS; ++ii) {
+        const int tl = RPI * ii + lane / CPR, pos = lane % CPR, T = 8 * wave + tl;
+        koff[ii] = tl * ROWB + 16 * (pos ^ swz_k(T));
+        voff[ii] = tl * ROWB + 16 * (pos ^ swz_v(T));
     }
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&lds[0];
-    // K A-operand reads: row 16 i + l16 (i = M tile, an immediate 4096 i), chunk 4 c + q4
-    uint32_t kaddr[NC];
+    // ---- prefix tile loads: this wave's 8 rows of tile `tile` into stage `st`
+    bool bad_page = false;
+    const char *const pk = reinterpret_cast<const char *>(PAGED ? a.k_pool : a.prefix_k);
+    const char *const pv = reinterpret_cast<const char *>(PAGED ? a.v_pool : a.prefix_v);
+    // paged: lane i holds the page id of this wave's rows of tile page_base + i (a scalar load per tile
+    // would put its latency into every step); prefix pages have the same ids in every branch's row
+    // (branch 0's is read)
+    int32_t page_ids = 0;
+    int page_base = s0;
+    auto request_pages = [&](int tile) INLINE {
+        page_base = tile;
+        const int i = (int)min((int64_t)(tile + lane) * (KT / kPageSize) + wave * 8 / kPageSize, (int64_t)a.max_pages - 1);
+        page_ids = a.page_table[i];
+        asm volatile("" : "+v"(page_ids));  // waited for here: a wait at each use would drain the tiles in flight
+    };
+    if constexpr (PAGED) request_pages(s0);
+    // `bytes` bytes of K and V rows into this wave's eight rows of stage st
+    auto load_rows = [&](const char *ksrc, const char *vsrc, int bytes, int st) INLINE {
+        const __amdgpu_buffer_rsrc_t rk = make_rsrc(ksrc, bytes), rv = make_rsrc(vsrc, bytes);
+        char *kd = &lds[st * KBYTES + 8 * wave * ROWB];
+        char *vd = &lds[V_LDS + st * KBYTES + 8 * wave * ROWB];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) kaddr[c] = lds0 + K_LDS + l16 * ROWB + 16 * ((4 * c + q4) ^ l16);
-    // V^T reads (transposed): lane (q4, l16) addresses row 4 q4 + l16 / 4, d = 16 e + 4 (l16 % 4);
-    // rows 16 m further are at + 4096 m with the same swizzle
-    uint32_t vaddr[NE];
-    {
-        const int jt = l16 >> 2, m4 = l16 & 3, T = 4 * q4 + jt;
+        for (int ii = 0; ii < DMAS; ++ii)
+            dma16<0>(rk, (lds_void *)(__attribute__((address_space(3))) char *)(kd + ii * RPI * ROWB), koff[ii]);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const int slot = (2 * e + (m4 >> 1)) ^ ((2 * T) & 15);
-            vaddr[e] = lds0 + V_LDS + T * ROWB + slot * 16 + (m4 & 1) * 8;
+        for (int ii = 0; ii < DMAS; ++ii)
+            dma16<0>(rv, (lds_void *)(__attribute__((address_space(3))) char *)(vd + ii * RPI * ROWB), voff[ii]);
+    };
+    // this wave's rows of a whole tile (without branches and in few scalar steps: they stand in every
+    // step of the inner loop)
+    const uint64_t page_bytes = (uint64_t)Hkv * kPageSize * ROWB;
+    const size_t wave_off = PAGED ? (size_t)g * kPageSize * ROWB + (8 * wave % kPageSize) * ROWB
+                                  : ((size_t)g * Lp + 8 * wave) * ROWB;
+    const char *const pkw = pk + wave_off, *const pvw = pv + wave_off;
+    auto issue_prefix = [&](int tile, int st) INLINE {
+        if constexpr (PAGED) {
+            const uint32_t page = (uint32_t)__builtin_amdgcn_readlane(page_ids, tile - page_base);
+            const bool bad = page >= (uint32_t)a.n_pool_pages;
+            bad_page |= bad;
+            const uint64_t off = page * page_bytes;
+            load_rows(bad ? pk : pkw + off, bad ? pv : pvw + off, bad ? 0 : 8 * ROWB, st);
+        } else {
+            const uint64_t off = (uint64_t)(uint32_t)tile * (KT * ROWB);
+            load_rows(pkw + off, pvw + off, 8 * ROWB, st);
         }
-    }
+    };
+    // the first tiles' loads go ahead of everything that they do not need
+    if (nmain > 0) issue_prefix(s0, 0);
+
+    const int row_a = mul_div(ug, a.n_units, a.unit_groups) * 32;
+    const int row_z = min(rows_head, mul_div(ug + 1, a.n_units, a.unit_groups) * 32);
+    const int br_a = row_a / G / n, seq_z = (row_z - 1) / G, br_z = seq_z / n;
+    const int tail0 = PT * KT, pre_groups = (Lp - tail0 + GRP - 1) / GRP;
+    // Lane i of a chunk of 64 branches: branch br_first + i's length before the instruction, and the
+    // inclusive scan of the branches' groups (br_base groups precede the chunk)
+    int br_len = 0, br_scan = 0, br_first = br_a, br_base = pre_groups, n_groups = 0;
+    auto request_branches = [&](int first) INLINE { return first + lane <= br_z ? a.suffix_len[first + lane] : 0; };
+    auto take_branches = [&](int first, int raw) INLINE {
+        const int b = first + lane;
+        br_len = min(max(raw, 0), a.max_suffix_len - n);
+        if (b <= br_z && br_len != raw) atomicOr(a.err, kErrSuffixClamped);
+        int x = b <= br_z ? (br_len + min(n - 1, seq_z - b * n) + GRP) / GRP : 0;  // (keys + 7) / 8, keys = len + t + 1
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(x, off);
+            if (lane >= off) x += y;
+        }
+        br_scan = x;
+        br_first = first;
+    };
+    const int raw_a = request_branches(br_a);
 
     // ---- query rows (B operand of S^T): lane holds unit row 16 t + l16, d = 32 c + 8 q4 .. +7
     bf16x8 qb[2][NC];
@@ -312,111 +456,175 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
     }
 
-    // ---- prefix tile loads: this wave's 8 rows of tile `tile` into stage `st`
-    bool bad_page = false;
-    const char *const pk = reinterpret_cast<const char *>(PAGED ? a.k_pool : a.prefix_k);
-    const char *const pv = reinterpret_cast<const char *>(PAGED ? a.v_pool : a.prefix_v);
-    auto issue_prefix = [&](int tile, int st) {
-        const int row0 = tile * KT + 8 * wave;
-        int rows_ok = max(0, min(8, Lp - row0));
-        size_t off;
-        if constexpr (PAGED) {
-            // prefix pages: the same ids in every branch's row (branch 0's row is read)
-            const int32_t page = scalar_load(a.page_table + uni(min(row0 / kPageSize, a.max_pages - 1)));
-            const bool bad = rows_ok > 0 && (page < 0 || page >= a.n_pool_pages);
-            bad_page |= bad;
-            rows_ok = bad ? 0 : rows_ok;
-            off = rows_ok > 0 ? (((size_t)page * Hkv + g) * kPageSize + (row0 % kPageSize)) * ROWB : 0;
-        } else {
-            off = rows_ok > 0 ? ((size_t)g * Lp + row0) * ROWB : 0;
-        }
-        const __amdgpu_buffer_rsrc_t rk = make_rsrc(pk + off, rows_ok * ROWB);
-        const __amdgpu_buffer_rsrc_t rv = make_rsrc(pv + off, rows_ok * ROWB);
-        char *kd = &lds[K_LDS + st * KBYTES + 8 * wave * ROWB];
-        char *vd = &lds[V_LDS + st * KBYTES + 8 * wave * ROWB];
-        dma16<0>(rk, (lds_void *)(__attribute__((address_space(3))) char *)kd, koff[0]);
-        dma16<0>(rk, (lds_void *)(__attribute__((address_space(3))) char *)(kd + 4 * ROWB), koff[1]);
-        dma16<0>(rv, (lds_void *)(__attribute__((address_space(3))) char *)vd, voff[0]);
-        dma16<0>(rv, (lds_void *)(__attribute__((address_space(3))) char *)(vd + 4 * ROWB), voff[1]);
-    };
+    if (nmain > 1) issue_prefix(s0 + 1, 1);
 
-    // ---- online softmax state: lane owns unit rows l16 (t = 0) and 16 + l16 (t = 1)
-    f32x4 acc[2][NE];
-    float m_ref[2], l_run[2];
+    // ---- per-lane constants
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&lds[0];
+    // K A-operand reads: row 16 i + l16 (i = M tile, an immediate), chunk 4 c + q4
+    uint32_t kaddr[NC];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        m_ref[t] = -INFINITY;
-        l_run[t] = 0.f;
+    for (int c = 0; c < NC; ++c) kaddr[c] = lds0 + l16 * ROWB + 16 * ((4 * c + q4) ^ swz_k(l16));
+    // V^T reads (transposed): lane (q4, l16) addresses row 4 q4 + l16 / 4, d = 16 e + 4 (l16 % 4); rows
+    // 16 m further are an immediate away with the same swizzle
+    uint32_t vaddr[NE];
+    {
+        const int m4 = l16 & 3, T = 4 * q4 + (l16 >> 2);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) acc[t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < NE; ++e)
+            vaddr[e] = lds0 + V_LDS + T * ROWB + 16 * ((2 * e + (m4 >> 1)) ^ swz_v(T)) + (m4 & 1) * 8;
     }
 
-    // Softmax of NM M tiles of scores (x[t][i][j]: row 16 t + l16, key 16 i + 4 q4 + j of the
-    // tile, raw q.k or -inf) into the two bf16 terms of P per k-step of 32 keys.
-    // Row tile t's maximum over NM M tiles of scores (xt[i][j]: key 16 i + 4 q4 + j of the tile,
-    // raw q.k or -inf), moving the running maximum (and rescaling) when it grows by over 2^8.
-    auto row_max = [&](auto NMc, int t, const float (&xt)[decltype(NMc)::value][4]) {
-        constexpr int NM = decltype(NMc)::value;
-        float v[4 * NM];
-#pragma unroll
-        for (int i = 0; i < NM; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[4 * i + j] = xt[i][j];
-        const float mx = max_over_rows(max_of(v)) * a.scale_log2;  // the scale is positive: the order is kept
-        const bool move = mx > m_ref[t] + kRescaleGap;
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(move) != 0, 0)) {
-            const float m_new = move ? mx : m_ref[t];
-            // exactly 1 for a row that keeps its max; 0 when the row's max was -inf
-            const float alpha = move ? fast_exp2(m_ref[t] - m_new) : 1.f;
-            l_run[t] *= alpha;
-            xdl_result_wait();
-#pragma unroll
-            for (int e = 0; e < NE; ++e) acc[t][e] *= alpha;
-            m_ref[t] = m_new;
-        }
-    };
-    // Row tile t's p = 2^(scale q.k - max) into the two bf16 terms per k-step of 32 keys.
-    auto row_exp = [&](auto NMc, int t, const float (&xt)[decltype(NMc)::value][4],
-                       bf16x8 (&pht)[decltype(NMc)::value / 2], bf16x8 (&plt)[decltype(NMc)::value / 2]) {
-        constexpr int NM = decltype(NMc)::value;
-        const float nm = (m_ref[t] == -INFINITY) ? 0.f : -m_ref[t];
-        float ps = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < NM / 2; ++kk) {
-            float p[8];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                p[j] = fast_exp2(__builtin_fmaf(xt[2 * kk][j], a.scale_log2, nm));
-                p[4 + j] = fast_exp2(__builtin_fmaf(xt[2 * kk + 1][j], a.scale_log2, nm));
+    // Tail tile j: this wave loads group 8 j + wave of the tail and leaves the group's branch (-1: the
+    // prefix, -2: no group) and limit in s_grp: a row of the branch with token t reads the group's
+    // keys k <= limit + t, every row those of the prefix with k <= limit.
+    auto issue_tail = [&](int j, int st) INLINE {
+        const int idx = j * NW + wave;
+        int b = -2, limit = -1, rows_ok = 0, pos = 0;
+        if (idx < pre_groups) {
+            b = -1;
+            pos = GRP * idx;
+            limit = Lp - tail0 - 1 - pos;
+            rows_ok = min(GRP, limit + 1);
+        } else if (idx < n_groups) {
+            int k = idx - br_base;
+            while (k >= __builtin_amdgcn_readlane(br_scan, 63)) {  // the next chunk of branches
+                br_base += __builtin_amdgcn_readlane(br_scan, 63);
+                k = idx - br_base;
+                take_branches(br_first + 64, request_branches(br_first + 64));
             }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) ps += p[j];
-            split_p(p, pht[kk], plt[kk]);
+            const int i = uni(__builtin_ctzll(__builtin_amdgcn_ballot_w64(br_scan > k)));
+            b = br_first + i;
+            const int L = __builtin_amdgcn_readlane(br_len, i);
+            const int keys = L + min(n - 1, seq_z - b * n) + 1;
+            pos = GRP * (k - (__builtin_amdgcn_readlane(br_scan, i) - (keys + GRP - 1) / GRP));
+            limit = L - pos;
+            rows_ok = min(GRP, keys - pos);
         }
-        l_run[t] += ps;
+        size_t off = 0;
+        if (rows_ok > 0) {
+            if constexpr (PAGED) {
+                const int at = b < 0 ? (tail0 + pos) / kPageSize : (Lp + kPageSize - 1) / kPageSize + pos / kPageSize;
+                const int32_t page = scalar_load(a.page_table + (size_t)max(b, 0) * a.max_pages + uni(min(at, a.max_pages - 1)));
+                const bool bad = page < 0 || page >= a.n_pool_pages;
+                bad_page |= bad;
+                rows_ok = bad ? 0 : rows_ok;
+                off = bad ? 0 : (((size_t)page * Hkv + g) * kPageSize + pos % kPageSize) * ROWB;
+            } else {
+                off = (b < 0 ? (size_t)g * Lp + tail0 + pos : ((size_t)b * Hkv + g) * a.suffix_cap + pos) * ROWB;
+            }
+        }
+        const bool pre = b < 0 || PAGED;
+        load_rows((pre ? pk : reinterpret_cast<const char *>(a.suffix_k)) + off,
+                  (pre ? pv : reinterpret_cast<const char *>(a.suffix_v)) + off, rows_ok * ROWB, st);
+        ds_write_b64((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&s_grp[st][wave],
+                     (uint64_t)(uint32_t)b | ((uint64_t)(uint32_t)limit << 32));
     };
-    auto softmax = [&](auto NMc, auto &x, auto &ph, auto &pl) {
+    // the range's share of the tail, now that the lengths are needed
+    take_branches(br_a, raw_a);
+    n_groups = pre_groups + __builtin_amdgcn_readlane(br_scan, 63);
+    if (br_z - br_a >= 64) {  // more branches than lanes: count the rest, then back to the first chunk
+        for (int first = br_a + 64; first <= br_z; first += 64) {
+            take_branches(first, request_branches(first));
+            n_groups += __builtin_amdgcn_readlane(br_scan, 63);
+        }
+        take_branches(br_a, request_branches(br_a));
+    }
+    const int tail_tiles = (n_groups + NW - 1) / NW, tail_each = tail_tiles / R, tail_more = tail_tiles - tail_each * R;
+    const int tail_pos = r >= pre_more ? r - pre_more : r - pre_more + R;
+    const int tail_t0 = tail_pos * tail_each + min(tail_pos, tail_more);
+    const int ntot = nmain + tail_each + (tail_pos < tail_more ? 1 : 0);
+    // paged: the page ids of the next n tiles from the range's tile i are in page_ids
+    auto have_pages = [&](int i, int n) INLINE {
+        if constexpr (PAGED)
+            if (s0 + i + n - page_base > 64) request_pages(s0 + i);
+    };
+    auto issue = [&](int i) INLINE {  // the range's tile i into buffer i mod 4
+        if (i < nmain) {
+            have_pages(i, 1);
+            issue_prefix(s0 + i, i % STAGES);
+        } else
+            issue_tail(tail_t0 + i - nmain, i % STAGES);
+    };
+
+    // ---- online softmax state: lane owns unit rows l16 (t = 0) and 16 + l16 (t = 1).  nm is minus
+    // the row's reference in log2 units, the maximum of the scores that last moved it: p = 2^(score -
+    // reference), sums and accumulator are relative to it.  +inf before the row's first key: p is then
+    // inf or NaN, which sends the tile to the path that sets a reference.
+    f32x4 acc[2][NE];
+    float nm[2] = {INFINITY, INFINITY}, l_run[2] = {0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) acc[t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // p of a tile's scores (x[t][4 i + j]: key 16 i + 4 q4 + j, raw q.k or -inf) against the references
+    // r as two bf16 terms per k-step of 32 keys, and this lane's sum of p per row.
+    auto exps = [&](const float (&x)[2][4 * MT], const float (&r)[2], bf16x8 (&ph)[2][KS], bf16x8 (&pl)[2][KS],
+                    float (&sum)[2]) INLINE {
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            row_max(NMc, t, x[t]);
-            row_exp(NMc, t, x[t], ph[t], pl[t]);
-        }
-    };
-
-    // p.v of one k-step (32 keys: tile keys 32 kk + 4 q4 + j and 32 kk + 16 + 4 q4 + j)
-    auto pv_step = [&](const vtr_t (&vr)[NE][2], const bf16x8 (&ph)[2], const bf16x8 (&pl)[2]) {
+            float ps[4];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const bf16x8 va = join_tr16(vr[e][0], vr[e][1]);
+            for (int kk = 0; kk < KS; ++kk) {
+                float p[8];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                acc[t][e] = mfma16(va, ph[t], acc[t][e]);
-                acc[t][e] = mfma16(va, pl[t], acc[t][e]);
+                for (int j = 0; j < 8; ++j) {
+                    p[j] = fast_exp2(__builtin_fmaf(x[t][8 * kk + j], a.scale_log2, r[t]));
+                    ps[j & 3] = (kk == 0 && j < 4) ? p[j] : ps[j & 3] + p[j];
+                }
+                split_p(p, ph[t][kk], pl[t][kk]);
             }
+            sum[t] = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+        }
+    };
+    // The references moved to the tile's maxima where these are higher, sums and accumulator rescaled.
+    auto move_reference = [&](const float (&x)[2][4 * MT], float (&r)[2]) INLINE {
+        float mx[2] = {max_of(x[0]), max_of(x[1])};
+        max_over_rows2(mx[0], mx[1]);
+        xdl_result_wait();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const float m_new = mx[t] * a.scale_log2;  // the scale is positive: the order is kept
+            const bool move = m_new > -nm[t];
+            // alpha: exactly 1 for a row that keeps its reference, 0 for a row's first keys
+            const float alpha = !move ? 1.f : nm[t] == INFINITY ? 0.f : fast_exp2(-nm[t] - m_new);
+            l_run[t] *= alpha;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) acc[t][e] *= alpha;
+            nm[t] = move ? -m_new : nm[t];
+            r[t] = nm[t] == INFINITY ? 0.f : nm[t];  // no key so far: every score is -inf
+        }
+    };
+    // A tile's softmax.  Any reference gives the same result while nothing overflows (all that it
+    // scales is in fp32), so p is taken against the old one and only a lane's sum past kRescaleLimit
+    // (or NaN) leads to the path with the maxima: a maximum per tile costs 26 of 250 vector issue
+    // slots, and beside a matrix wave those bound the step.
+    auto softmax = [&](const float (&x)[2][4 * MT], bf16x8 (&ph)[2][KS], bf16x8 (&pl)[2][KS]) INLINE {
+        float sum[2];
+        exps(x, nm, ph, pl, sum);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(sum[0] + sum[1] <= kRescaleLimit)) != 0, 0)) {
+            float r[2];
+            move_reference(x, r);
+            exps(x, r, ph, pl, sum);
+        }
+        l_run[0] += sum[0];
+        l_run[1] += sum[1];
+    };
+
+    // p.v of EG d tiles from e0 and one k-step (32 keys: 4 q4 + j and 16 + 4 q4 + j)
+    auto pv_mfma = [&](auto E0c, const vtr_t (&v)[EG][2], const bf16x8 (&ph)[2], const bf16x8 (&pl)[2]) INLINE {
+        constexpr int e0 = decltype(E0c)::value;
+#pragma unroll
+        for (int e = 0; e < EG; ++e) {
+            const bf16x8 va = join_tr16(v[e][0], v[e][1]);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[t][e0 + e] = mfma16(va, ph[t], acc[t][e0 + e]);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[t][e0 + e] = mfma16(va, pl[t], acc[t][e0 + e]);
         }
     };
 
-    // ---- the prefix range: tiles [t0, t1), two loading ahead, in two phases per tile.  The two
+    // ---- the range's tiles, two loading ahead, in two phases per tile.  The two
     // waves of a SIMD alternate between matrix and vector work: in phase 1 of step i the first
     // wave (waves 0..3) takes p.v of tile i - 1 and q.k of tile i while the second (waves 4..7)
     // takes the softmax of tile i - 1; in phase 2 the first takes the softmax of tile i while the
@@ -424,320 +632,286 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // are not live together).  A block barrier separates the phases; the
     // wave in its matrix phase runs at raised priority.  Four tile buffers: tiles i - 1 and i are
     // read during step i while i + 1 and i + 2 load.
-    using nm4_t = std::integral_constant<int, 4>;
-    // q.k of the tile at buffer offset SO: each M tile's K operands are read one M tile ahead of
-    // its MFMAs (LDS reads return in order, so "at most 4 outstanding" means the earlier M tile's
-    // four reads are in)
-    auto qk = [&](auto SOc, f32x4 (&sc)[4][2]) {
-        constexpr int SO = decltype(SOc)::value;
-        bf16x8 ka[2][NC];
-        auto rd = [&](auto MIc) {
-            constexpr int mi = decltype(MIc)::value;
+    //
+    constexpr int NG = KS * (NE / EG);  // groups of V operands per tile
+    using plan = MatrixPlan<NG, MT, 2 * EG, NC>;
+    auto read_v = [&](auto SOc, auto Gc, uint32_t dyn, vtr_t (&v)[EG][2]) INLINE {
+        constexpr int kk = decltype(Gc)::value / (NE / EG), e0 = decltype(Gc)::value % (NE / EG) * EG;
+        constexpr int o = decltype(SOc)::value + kk * 32 * ROWB;
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
-                ka[mi & 1][c] = __builtin_bit_cast(bf16x8, ds_read_b128_at<SO + mi * 16 * ROWB>(kaddr[c]));
+        for (int e = 0; e < EG; ++e) {
+            v[e][0] = ds_read_tr16<o>(vaddr[e0 + e] + dyn);
+            v[e][1] = ds_read_tr16<o + 16 * ROWB>(vaddr[e0 + e] + dyn);
+        }
+    };
+    auto read_k = [&](auto SOc, auto Mc, uint32_t dyn, bf16x8 (&k)[NC]) INLINE {
+        constexpr int o = decltype(SOc)::value + decltype(Mc)::value * 16 * ROWB;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) k[c] = __builtin_bit_cast(bf16x8, ds_read_b128_at<o>(kaddr[c] + dyn));
+    };
+    auto tie_v = [&](vtr_t (&v)[EG][2]) INLINE {
+#pragma unroll
+        for (int e = 0; e < EG; ++e) asm volatile("" : "+v"(v[e][0]), "+v"(v[e][1]));
+    };
+    auto tie_k = [&](bf16x8 (&k)[NC]) INLINE {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(k[c]));
+    };
+    auto qk_group = [&](auto Mc, const bf16x8 (&k)[NC], f32x4 (&sc)[2][MT]) INLINE {
+        constexpr int mi = decltype(Mc)::value;
+        sc[0][mi] = sc[1][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) sc[t][mi] = mfma16(k[c], qb[t][c], sc[t][mi]);
+    };
+    // p.v of the tile at buffer offset SOP (PV) and q.k of the one at SO + dyn.
+    auto matrix = [&](auto PVc, auto SOc, auto SOPc, uint32_t dyn, f32x4 (&sc)[2][MT], const bf16x8 (&ph)[2][KS],
+                      const bf16x8 (&pl)[2][KS]) INLINE {
+        constexpr int first = decltype(PVc)::value ? 0 : NG, last = NG + MT;  // groups: V 0..NG-1, K NG..NG+MT-1
+        constexpr int SETS = plan::AHEAD + 1;
+        vtr_t v[SETS][EG][2];
+        bf16x8 k[SETS][NC];
+        auto request = [&](auto Jc) INLINE {
+            constexpr int j = decltype(Jc)::value;
+            if constexpr (j < NG)
+                read_v(SOPc, Jc, 0u, v[j % SETS]);
+            else
+                read_k(SOc, std::integral_constant<int, j - NG>{}, dyn, k[(j - NG) % SETS]);
         };
-        rd(std::integral_constant<int, 0>{});
-        static_for<4>([&](auto MIc) {
-            constexpr int mi = decltype(MIc)::value;
-            if constexpr (mi + 1 < 4) {
-                rd(std::integral_constant<int, mi + 1>{});
-                asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
+        static_for<last - first>([&](auto Ic) INLINE {
+            constexpr int q = first + decltype(Ic)::value;
+            static_for<last - first>([&](auto Jc) INLINE {
+                constexpr int j = first + decltype(Jc)::value;
+                if constexpr (plan::due(j, first) == q) request(std::integral_constant<int, j>{});
+            });
+            lds_wait_to<plan::behind(q, first)>();
+            if constexpr (q < NG)
+                tie_v(v[q % SETS]);
+            else
+                tie_k(k[(q - NG) % SETS]);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (q < NG) {
+                constexpr int kk = q / (NE / EG);
+                const bf16x8 h2[2] = {ph[0][kk], ph[1][kk]}, l2[2] = {pl[0][kk], pl[1][kk]};
+                pv_mfma(std::integral_constant<int, q % (NE / EG) * EG>{}, v[q % SETS], h2, l2);
             } else {
-                lds_wait();
+                qk_group(std::integral_constant<int, q - NG>{}, k[(q - NG) % SETS], sc);
             }
-#pragma unroll
-            for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(ka[mi & 1][c]));
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = 0; c < NC; ++c) v = mfma16(ka[mi & 1][c], qb[t][c], v);
-                sc[mi][t] = v;
-            }
+            __builtin_amdgcn_sched_barrier(0);
         });
     };
-    // (every tile here is whole: no key mask, which would make the compiler copy the scores
-    // into the masked path's registers, 32 moves per tile)
-    auto sm = [&](const f32x4 (&sc)[4][2], bf16x8 (&ph)[2][2], bf16x8 (&pl)[2][2]) {
+    // (every tile of the inner loop is whole: no key mask, which would make the compiler copy the
+    // scores into the masked path's registers)
+    auto sm = [&](const f32x4 (&sc)[2][MT], bf16x8 (&ph)[2][KS], bf16x8 (&pl)[2][KS], auto &&also) INLINE {
         xdl_result_wait();
-        float x[2][4][4];
+        also();
+        float x[2][4 * MT];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[t][mi][j] = sc[mi][t][j];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            row_max(nm4_t{}, t, x[t]);
-            row_exp(nm4_t{}, t, x[t], ph[t], pl[t]);
-        }
+            for (int i = 0; i < 4 * MT; ++i) x[t][i] = sc[t][i >> 2][i & 3];
+        softmax(x, ph, pl);
     };
-    auto pv_tile = [&](auto SOc, const bf16x8 (&ph)[2][2], const bf16x8 (&pl)[2][2]) {
-        constexpr int SO = decltype(SOc)::value;
-        static_for<2>([&](auto KKc) {
-            constexpr int kk = decltype(KKc)::value;
-            vtr_t vr[NE][2];
-#pragma unroll
-            for (int e = 0; e < NE; ++e) {
-                vr[e][0] = ds_read_tr16<SO + (2 * kk) * 16 * ROWB>(vaddr[e]);
-                vr[e][1] = ds_read_tr16<SO + (2 * kk + 1) * 16 * ROWB>(vaddr[e]);
-            }
-            lds_wait();
-#pragma unroll
-            for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(vr[e][0]), "+v"(vr[e][1]));
-            const bf16x8 h2[2] = {ph[0][kk], ph[1][kk]}, l2[2] = {pl[0][kk], pl[1][kk]};
-            pv_step(vr, h2, l2);
-        });
-    };
-    f32x4 sc[4][2];
-    bf16x8 ph[2][2], pl[2][2];
-    // step i (0 <= i <= ntile; the last one only finishes tile ntile - 1), tile i in buffer B.  The
-    // two roles run in loops of their own (a role test in each phase would keep both roles'
-    // values live at once); both pass the same barriers.
-    auto step = [&](int i, auto Bc, auto LEADc) {
+    f32x4 sc[2][MT];
+    bf16x8 ph[2][KS], pl[2][KS];
+    using zero = std::integral_constant<int, 0>;
+    // Step i of the inner loop, tile i in buffer B = i mod 4: q.k of tile i, p.v of tile i - 1 and the
+    // load of tile i + 2, all whole prefix tiles.  The two roles run in loops of their own (a role
+    // test in each phase would keep both roles' values live at once); both pass the same barriers.
+    auto step = [&](int i, auto Bc, auto LEADc) INLINE {
         constexpr int B = decltype(Bc)::value;
         constexpr bool LEAD = decltype(LEADc)::value;
-        constexpr int SO = B * KBYTES, SOP = ((B + STAGES - 1) % STAGES) * KBYTES;
-        using so_t = std::integral_constant<int, SO>;
-        using sop_t = std::integral_constant<int, SOP>;
-        if (i < ntile) {
-            if (i + 1 < ntile)
-                wait_vm<4>();
+        using so_t = std::integral_constant<int, B * KBYTES>;
+        using sop_t = std::integral_constant<int, ((B + STAGES - 1) % STAGES) * KBYTES>;
+        auto mat = [&]() INLINE {
+            __builtin_amdgcn_s_setprio(1);
+            matrix(std::true_type{}, so_t{}, sop_t{}, 0u, sc, ph, pl);
+            __builtin_amdgcn_s_setprio(0);
+        };
+        // the load of tile i + 2, among the softmax's vector work: in front of a matrix phase its scalar
+        // work would hold up the products
+        auto load = [&]() INLINE { issue_prefix(s0 + i + 2, (B + 2) % STAGES); };
+        auto vec = [&]() INLINE {
+            if (active)
+                sm(sc, ph, pl, load);
             else
-                wait_vm<0>();
-        }
+                load();
+        };
+        wait_vm<2 * DMAS>();
         lds_barrier();  // tile i is in LDS; every wave is done with tile i - 2
-        if (i + 2 < ntile) issue_prefix(t0 + i + 2, (i + 2) % STAGES);
-        if (active) {
-            if constexpr (LEAD) {
-                __builtin_amdgcn_s_setprio(1);
-                if (i > 0) pv_tile(sop_t{}, ph, pl);
-                if (i < ntile) qk(so_t{}, sc);
-                __builtin_amdgcn_s_setprio(0);
-            } else {
-                if (i > 0) sm(sc, ph, pl);
+        if constexpr (LEAD) {
+            if (active) mat();
+        } else {
+            vec();
+        }
+        lds_barrier();
+        if constexpr (LEAD)
+            vec();
+        else if (active)
+            mat();
+    };
+
+    // ---- the same step for any tile: the first (no p.v), the last (only p.v) and those of the tail,
+    // where a wave skips a tile none of its rows reads (use) and masks the keys of each group past
+    // each row's limit.  What follows describes the tile whose q.k was last taken.
+    // A lane's four keys of score tile i are keys 4 (q4 mod 2) + j of group 2 i + q4 / 2.
+    bool use = true, tail = false;
+    int lim[2][MT];  // row t reads the keys k <= lim[t][i] of group 2 i + q4 / 2
+#pragma unroll
+    for (int i = 0; i < MT; ++i) lim[0][i] = lim[1][i] = KT;
+    int row_bt[2];  // the rows' branch (past every branch beyond the head's rows) << 16 | token
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int lr = u * 32 + 16 * t + l16;
+        row_bt[t] = lr < rows_head ? ((lr / G) / n) << 16 | ((lr / G) % n) : 0x7fff0000;
+    }
+    const uint32_t grp0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&s_grp[0][0] + 8 * (q4 >> 1);
+    auto any_qk = [&](int i) INLINE {
+        use = true;
+        tail = i >= nmain;
+        if (!tail) {
+#pragma unroll
+            for (int q = 0; q < MT; ++q) lim[0][q] = lim[1][q] = KT;
+        } else {
+            uint64_t d[MT];
+            static_for<MT>([&](auto Qc) INLINE {
+                constexpr int q = decltype(Qc)::value;
+                d[q] = ds_read_b64_at<16 * q>(grp0 + (i % STAGES) * (uint32_t)sizeof(s_grp[0]));
+            });
+            lds_wait();
+#pragma unroll
+            for (int q = 0; q < MT; ++q) asm volatile("" : "+v"(d[q]));
+            int most = -1;
+#pragma unroll
+            for (int q = 0; q < MT; ++q) {
+                const int b = (int)(uint32_t)d[q], base = (int)(d[q] >> 32);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    lim[t][q] = b == -1 ? base : b == row_bt[t] >> 16 ? base + (row_bt[t] & 0xffff) : -1;
+                    most = max(most, lim[t][q]);
+                }
             }
+            use = __builtin_amdgcn_ballot_w64(most >= 0) != 0;
+        }
+        if (use) matrix(std::false_type{}, zero{}, zero{}, (uint32_t)(i % STAGES) * KBYTES, sc, ph, pl);
+    };
+    auto any_sm = [&]() INLINE {
+        if (!use) return;
+        xdl_result_wait();
+        float x[2][4 * MT];
+        const int k0 = 4 * ((opaque_lane_id() >> 4) & 1);  // the lane's first key of its groups
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4 * MT; ++i)
+                x[t][i] = (k0 + (i & 3) <= lim[t][i >> 2]) ? sc[t][i >> 2][i & 3] : -INFINITY;
+        softmax(x, ph, pl);
+    };
+    auto any_pv = [&](int i) INLINE {
+        if (!use) return;
+        const uint32_t dyn = (uint32_t)(i % STAGES) * KBYTES;
+        constexpr int PG = NE < 4 ? NE : 4, GS = PG / EG;  // d tiles per round of reads
+        static_for<KS * (NE / PG)>([&](auto Rc) INLINE {
+            constexpr int kk = decltype(Rc)::value / (NE / PG), q0 = decltype(Rc)::value * GS;
+            vtr_t v[GS][EG][2];
+            static_for<GS>([&](auto Gc) INLINE {
+                read_v(zero{}, std::integral_constant<int, q0 + decltype(Gc)::value>{}, dyn, v[decltype(Gc)::value]);
+            });
+            lds_wait();
+            static_for<GS>([&](auto Gc) INLINE { tie_v(v[decltype(Gc)::value]); });
+            if (tail) {
+                // A non-finite value of a group is zeroed for the product and the rows that read its key
+                // are made NaN (through their sums), so that it reaches no row of another branch or of
+                // an earlier token (a masked row's p is 0, and 0 times such a value would be NaN).
+                uint32_t bits = 0;
+#pragma unroll
+                for (int e = 0; e < PG; ++e)
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        const uint64_t w = (uint64_t)v[e / EG][e % EG][y];
+                        bits |= (((uint32_t)w & 0x7f807f80u) + 0x00800080u) |
+                                ((((uint32_t)(w >> 32)) & 0x7f807f80u) + 0x00800080u);
+                    }
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64((bits & 0x80008000u) != 0) != 0, 0)) {
+                    // read y holds keys k0 + k (k = 0..3) of group 2 (2 kk + y) + q4 / 2, a half wave's group
+                    const int k0 = 4 * ((opaque_lane_id() >> 4) & 1);
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        int first = 0x7fffffff;
+#pragma unroll
+                        for (int e = 0; e < PG; ++e) {
+                            uint64_t w = (uint64_t)v[e / EG][e % EG][y];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                if (((uint32_t)(w >> (16 * k)) & 0x7f80u) == 0x7f80u) {
+                                    first = min(first, k0 + k);
+                                    w &= ~((uint64_t)0xffffu << (16 * k));
+                                }
+                            v[e / EG][e % EG][y] = (vtr_t)w;
+                        }
+#pragma unroll
+                        for (int off = 1; off < 32; off <<= 1) first = min(first, __shfl_xor(first, off));
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+                            l_run[t] = lim[t][2 * kk + y] >= first ? __builtin_nanf("") : l_run[t];
+                    }
+                }
+            }
+            const bf16x8 h2[2] = {ph[0][kk], ph[1][kk]}, l2[2] = {pl[0][kk], pl[1][kk]};
+            static_for<GS>([&](auto Gc) INLINE {
+                constexpr int q = q0 + decltype(Gc)::value;
+                pv_mfma(std::integral_constant<int, q % (NE / EG) * EG>{}, v[decltype(Gc)::value], h2, l2);
+            });
+        });
+    };
+    auto any_step = [&](int i, auto LEADc) INLINE {
+        constexpr bool LEAD = decltype(LEADc)::value;
+        auto mat = [&]() INLINE {
+            __builtin_amdgcn_s_setprio(1);
+            if (i > 0) any_pv(i - 1);
+            if (i < ntot) any_qk(i);
+            __builtin_amdgcn_s_setprio(0);
+        };
+        if (i + 1 < ntot)
+            wait_vm<2 * DMAS>();
+        else
+            wait_vm<0>();
+        lds_barrier();
+        if (i + 2 < ntot) issue(i + 2);
+        if (active) {
+            if constexpr (LEAD)
+                mat();
+            else if (i > 0)
+                any_sm();
         }
         lds_barrier();
         if (active) {
-            if constexpr (LEAD) {
-                if (i < ntile) sm(sc, ph, pl);
-            } else {
-                __builtin_amdgcn_s_setprio(1);
-                if (i > 0) pv_tile(sop_t{}, ph, pl);
-                if (i < ntile) qk(so_t{}, sc);
-                __builtin_amdgcn_s_setprio(0);
-            }
+            if constexpr (!LEAD)
+                mat();
+            else if (i < ntot)
+                any_sm();
         }
     };
-    auto run = [&](auto LEADc) {
-        for (int i = 0; i <= ntile; i += STAGES) {
-            step(i, std::integral_constant<int, 0>{}, LEADc);
-            if (i + 1 <= ntile) step(i + 1, std::integral_constant<int, 1>{}, LEADc);
-            if (i + 2 <= ntile) step(i + 2, std::integral_constant<int, 2>{}, LEADc);
-            if (i + 3 <= ntile) step(i + 3, std::integral_constant<int, 3>{}, LEADc);
+    auto run = [&](auto LEADc) INLINE {
+        any_step(0, LEADc);
+        int i = 1;
+        for (; i + 5 < nmain; i += STAGES) {  // (exits within the four steps made the compiler spill)
+            have_pages(i + 2, STAGES);
+            step(i, std::integral_constant<int, 1>{}, LEADc);
+            step(i + 1, std::integral_constant<int, 2>{}, LEADc);
+            step(i + 2, std::integral_constant<int, 3>{}, LEADc);
+            step(i + 3, std::integral_constant<int, 0>{}, LEADc);
         }
+        for (; i <= ntot; ++i) any_step(i, LEADc);
     };
-    if (ntile > 0) issue_prefix(t0, 0);
-    if (ntile > 1) issue_prefix(t0 + 1, 1);
-    if (ntile > 0) {
+    if (ntot > 0) {
+        if (nmain < 1) issue(0);
+        if (nmain < 2 && ntot > 1) issue(1);
         if (wave < 4)
             run(std::true_type{});
         else
             run(std::false_type{});
-    }
-
-    // ---- keys outside the whole prefix tiles (last range only), per wave: the prefix's last
-    // Lp mod 64 keys (every row reads them), then the suffix keys branch by branch of the unit's
-    // rows (the waves of a block hold different branches)
-    if (r == R - 1) {
-        lds_barrier();  // every wave is done with the stage buffers (no DMA in flight: all waited)
-        if (active) {
-            const int lr0 = u * 32, lr1 = min(rows_head, lr0 + 32);
-            const int s_lo = lr0 / G, s_hi = (lr1 - 1) / G;
-            const int b_lo = s_lo / n, b_hi = s_hi / n;
-            // this lane's rows: sequence (or -1 past the head's rows)
-            int srow[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int lr = lr0 + 16 * t + l16;
-                srow[t] = lr < rows_head ? lr / G : -1;
-            }
-            const int max_L = a.max_suffix_len - n;  // clamp bound of suffix_len[b]
-            const uint32_t vw = lds0 + wave * SUF_LDS;  // this wave's V area
-            char *vwp = &lds[wave * SUF_LDS];
-            // V DMA offsets for a 32-row suffix tile: instruction ii writes rows 4 ii + lane / 16
-            // (the parity of ii decides the swizzle); rows 16 m further are one page further
-            uint32_t svoff[2];
-#pragma unroll
-            for (int par = 0; par < 2; ++par) {
-                const int T = 4 * par + (lane >> 4), pos = lane & 15;
-                svoff[par] = (lane >> 4) * ROWB + 16 * (pos ^ ((2 * T) & 15));
-            }
-            const char *const sk = reinterpret_cast<const char *>(PAGED ? a.k_pool : a.suffix_k);
-            const char *const sv = reinterpret_cast<const char *>(PAGED ? a.v_pool : a.suffix_v);
-            const int pre_pages = (Lp + kPageSize - 1) / kPageSize;
-            // One 32-key tile [p0, p0 + 32) of a key run whose 16-row groups `grp` addresses (K from
-            // srck, V from srcv), row t of this lane masked to the run's keys <= lim[t] (-1: none).
-            // CHECK: a non-finite value is zeroed for the product and the first key holding one
-            // is kept in kbad.
-            auto key_tile = [&](auto CHECKc, auto &grp, const char *srck, const char *srcv, int p0, const int (&lim)[2],
-                                int &kbad) {
-                constexpr bool CHECK = decltype(CHECKc)::value;
-                // K rows straight into registers (A operand): M tile mi = rows 16 mi + l16
-                bf16x8 ka[2][NC];
-#pragma unroll
-                for (int mi = 0; mi < 2; ++mi) {
-                    const __amdgpu_buffer_rsrc_t rk = grp(srck, p0 + 16 * mi);
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-                        ka[mi][c] = __builtin_bit_cast(
-                            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, l16 * ROWB + 16 * (4 * c + q4), 0, 0));
-                }
-                // V rows into this wave's LDS area
-                {
-                    const __amdgpu_buffer_rsrc_t r0 = grp(srcv, p0), r1 = grp(srcv, p0 + 16);
-                    static_for<8>([&](auto I) {
-                        constexpr int ii = decltype(I)::value;
-                        constexpr int imm = 1024 * (ii % 4);
-                        dma16<imm>(ii < 4 ? r0 : r1,
-                                   (lds_void *)((__attribute__((address_space(3))) char *)vwp + 1024 * ii - imm),
-                                   svoff[ii & 1]);
-                    });
-                }
-                wait_vm<0>();
-                f32x4 sc[2][2];
-#pragma unroll
-                for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int c = 0; c < NC; ++c) s = mfma16(ka[mi][c], qb[t][c], s);
-                        sc[mi][t] = s;
-                    }
-                xdl_result_wait();
-                float x[2][2][4];
-                {
-                    const int kq = p0 + 4 * (opaque_lane_id() >> 4);  // key of j = 0 in M tile 0
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j)
-                                x[t][mi][j] = (kq + 16 * mi + j <= lim[t]) ? sc[mi][t][j] : -INFINITY;
-                }
-                bf16x8 ph[2][1], pl[2][1];
-                softmax(std::integral_constant<int, 2>{}, x, ph, pl);
-                vtr_t vr[NE][2];
-#pragma unroll
-                for (int e = 0; e < NE; ++e) {
-                    const uint32_t ad = vaddr[e] - (lds0 + V_LDS) + vw;
-                    vr[e][0] = ds_read_tr16<0>(ad);
-                    vr[e][1] = ds_read_tr16<16 * ROWB>(ad);
-                }
-                lds_wait();
-#pragma unroll
-                for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(vr[e][0]), "+v"(vr[e][1]));
-                if constexpr (CHECK) {
-                    // non-finite values: zero for the product, remember the first such key
-                    uint32_t bits = 0;
-#pragma unroll
-                    for (int e = 0; e < NE; ++e)
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            const uint64_t w = (uint64_t)vr[e][h];
-                            bits |= (((uint32_t)w & 0x7f807f80u) + 0x00800080u) |
-                                    ((((uint32_t)(w >> 32)) & 0x7f807f80u) + 0x00800080u);
-                        }
-                    if (__builtin_expect(__builtin_amdgcn_ballot_w64((bits & 0x80008000u) != 0) != 0, 0)) {
-                        // lane (q4, l16) holds keys p0 + 16 h + 4 q4 + k (k = 0..3) of column 16 e + l16
-                        int first = 0x7fffffff;
-                        const int kq = p0 + 4 * (opaque_lane_id() >> 4);
-#pragma unroll
-                        for (int e = 0; e < NE; ++e)
-#pragma unroll
-                            for (int h = 0; h < 2; ++h) {
-                                uint64_t w = (uint64_t)vr[e][h];
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) {
-                                    const uint32_t v16 = (uint32_t)(w >> (16 * k)) & 0xffffu;
-                                    if ((v16 & 0x7f80u) == 0x7f80u) {
-                                        first = min(first, kq + 16 * h + k);
-                                        w &= ~((uint64_t)0xffffu << (16 * k));
-                                    }
-                                }
-                                vr[e][h] = (vtr_t)w;
-                            }
-#pragma unroll
-                        for (int off = 1; off < 64; off <<= 1) first = min(first, __shfl_xor(first, off));
-                        kbad = min(kbad, first);
-                    }
-                }
-                const bf16x8 h2[2] = {ph[0][0], ph[1][0]}, l2[2] = {pl[0][0], pl[1][0]};
-                pv_step(vr, h2, l2);
-                // the next tile's V overwrites this area: the transposed reads are done
-                // (waited above) before its DMA is issued
-            };
-            // the prefix keys past its whole tiles: rows of KV head g, or the prefix pages (the
-            // same ids in every branch's row: branch 0's row is read)
-            const int tail0 = PT * KT, tl = Lp - tail0;
-            if (tl > 0) {
-                auto grp_pre = [&](const char *src, int p) -> __amdgpu_buffer_rsrc_t {
-                    int rows_ok = max(0, min(kPageSize, tl - p));
-                    size_t off;
-                    if constexpr (PAGED) {
-                        const int32_t page = scalar_load(a.page_table + uni(min((tail0 + p) / kPageSize, a.max_pages - 1)));
-                        const bool bad = rows_ok > 0 && (page < 0 || page >= a.n_pool_pages);
-                        bad_page |= bad;
-                        rows_ok = bad ? 0 : rows_ok;
-                        off = rows_ok > 0 ? ((size_t)page * Hkv + g) * kPageSize * ROWB : 0;
-                    } else {
-                        off = rows_ok > 0 ? ((size_t)g * Lp + tail0 + p) * ROWB : 0;
-                    }
-                    return make_rsrc(src + off, rows_ok * ROWB);
-                };
-                int lim[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) lim[t] = srow[t] >= 0 ? tl - 1 : -1;
-                int unused = 0x7fffffff;
-                for (int p0 = 0; p0 < tl; p0 += ST) key_tile(std::false_type{}, grp_pre, pk, pv, p0, lim, unused);
-            }
-            for (int b = b_lo; b <= b_hi; ++b) {
-                const int lraw = scalar_load(a.suffix_len + b);
-                const int L = min(max(lraw, 0), max_L);
-                if (L != lraw && lane == 0) atomicOr(a.err, kErrSuffixClamped);
-                const int tmax = min(n - 1, s_hi - b * n);
-                const int klim = L + tmax + 1;  // keys of b's suffix this unit reads
-                // the last key each of this lane's rows reads, or -1 for a row of another branch
-                int lim[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) lim[t] = (srow[t] >= 0 && srow[t] / n == b) ? L + srow[t] % n : -1;
-                int kbad = 0x7fffffff;  // first key of b holding a non-finite value
-                // 16-row group resource of b's suffix positions [p, p + 16)
-                auto grp = [&](const char *src, int p) -> __amdgpu_buffer_rsrc_t {
-                    int rows_ok = max(0, min(kPageSize, klim - p));
-                    size_t off;
-                    if constexpr (PAGED) {
-                        const int32_t page = scalar_load(
-                            a.page_table + (size_t)b * a.max_pages + uni(min(pre_pages + p / kPageSize, a.max_pages - 1)));
-                        const bool bad = rows_ok > 0 && (page < 0 || page >= a.n_pool_pages);
-                        bad_page |= bad;
-                        rows_ok = bad ? 0 : rows_ok;
-                        off = rows_ok > 0 ? ((size_t)page * Hkv + g) * kPageSize * ROWB : 0;
-                    } else {
-                        off = rows_ok > 0 ? (((size_t)b * Hkv + g) * a.suffix_cap + p) * ROWB : 0;
-                    }
-                    return make_rsrc(src + off, rows_ok * ROWB);
-                };
-                for (int p0 = 0; p0 < klim; p0 += ST) key_tile(std::true_type{}, grp, sk, sv, p0, lim, kbad);
-#pragma unroll
-                for (int t = 0; t < 2; ++t) l_run[t] = (lim[t] >= kbad) ? __builtin_nanf("") : l_run[t];
-            }
-        }
     }
     if (PAGED && __builtin_amdgcn_ballot_w64(bad_page) != 0 && lane == 0) atomicOr(a.err, kErrBadPage);
 
@@ -760,7 +934,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         float *dst = a.part_o + orow * HD + 4 * q4c;
 #pragma unroll
         for (int e = 0; e < NE; ++e) *reinterpret_cast<f32x4 *>(dst + 16 * e) = acc[t][e] * inv;
-        if (q4c == 0) a.part_lse[orow] = empty ? -INFINITY : (m_ref[t] + __log2f(l)) * kLn2;
+        if (q4c == 0) a.part_lse[orow] = empty ? -INFINITY : (__log2f(l) - nm[t]) * kLn2;
     }
 }
 
@@ -772,8 +946,8 @@ int prefill_tiles_waves() { return NW; }
 int prefill_tiles_blocks_per_cu(bool paged)
 {
     int n = 0;
-    const void *f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<true>)
-                          : reinterpret_cast<const void *>(&prefill_tiles_kernel<false>);
+    const void *f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<128, true>)
+                          : reinterpret_cast<const void *>(&prefill_tiles_kernel<128, false>);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * NW, 0) != hipSuccess) return 0;
     return n;
 }
@@ -782,9 +956,9 @@ hipError_t launch_prefill_tiles(const PrefillArgs &a, int n_blocks, hipStream_t 
 {
     if (n_blocks <= 0) return hipSuccess;
     if (a.paged)
-        prefill_tiles_kernel<true><<<n_blocks, 64 * NW, 0, s>>>(a);
+        prefill_tiles_kernel<128, true><<<n_blocks, 64 * NW, 0, s>>>(a);
     else
-        prefill_tiles_kernel<false><<<n_blocks, 64 * NW, 0, s>>>(a);
+        prefill_tiles_kernel<128, false><<<n_blocks, 64 * NW, 0, s>>>(a);
     return hipGetLastError();
 }
 

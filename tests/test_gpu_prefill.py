@@ -206,8 +206,48 @@ def test_prefill_tiled_edges(fa, c):
     """The tiled kernel (at least 256 rows per KV head) with no prefix at all (the suffix keys
     only), with an explicit grid of one prefix range, with G = 1 and 2-token instructions of
     256 branches, where a 32-row unit holds 16 branches (each masked to its own suffix), and with a
-    prefix shorter than one 64-key tile (no whole tile: every prefix key on the per-wave path)."""
+    prefix shorter than one 64-key tile (no whole tile: every prefix key in the masked tail tiles)."""
     _check_case(fa, c)
+
+
+def _scored(w, how):
+    """The workload with scores of +-100s (natural log units) that move along the keys: rising or
+    falling with the position, or a first 64-key tile far below or far above every later key."""
+    f32 = W.bf16_to_f32
+    Lp = w.prefix_len
+    if how in ("rising", "falling"):
+        ramp = np.exp2(np.floor(np.arange(Lp) * 7.0 / Lp)).astype(np.float32)
+        w.prefix_k[:] = W.bf16_bits(f32(w.prefix_k) * (ramp if how == "rising" else ramp[::-1])[None, :, None])
+        return
+    w.step_q[:] = W.bf16_bits(np.abs(f32(w.step_q)))
+    k = np.abs(f32(w.prefix_k)) * np.float32(8.0 if how == "high-first" else 1.0)
+    k[:, :64] *= np.float32(4.0)
+    k[:, 64 if how == "high-first" else 0:Lp if how == "high-first" else 64] *= np.float32(-1.0)
+    w.prefix_k[:] = W.bf16_bits(k)
+
+
+@pytest.mark.parametrize("how", ["rising", "falling", "low-first", "high-first"])
+def test_prefill_tiled_moving_reference(fa, how):
+    """The tiled kernel takes its exponentials against a row's old reference and moves it only when
+    they have grown past a limit: scores that climb by hundreds along the keys (p overflows against
+    the old reference), that fall (p underflows), and a first tile far below or above the rest; a
+    prefix of whole tiles and 37 more keys, suffixes of 300-330 keys, whose tail tiles are shared by
+    all ranges.  Every row checked, contiguous and paged."""
+    n = 20
+    w = W.make(W.CONFIGS["mid"].replace(n_kv_heads=2, n_q_heads=8, n_branches=4, prefix_len=1509,
+                                        suffix_range=(300, 330), steps=n, seed=2765))
+    _scored(w, how)
+    q, sk, sv = _instruction(w, n)
+    ref, ref_lse = _reference(w, n, q, sk, sv)
+    plan, out, lse = _run(fa, w, n, q, sk, sv)
+    pplan, pout, plse = _run_paged(fa, w, n, q, sk, sv, seed=2766)
+    assert plan.info().units_per_block == 8 and plan.info().n_slots > 1
+    for what, o, l in (("contiguous", out, lse), ("paged", pout, plse)):
+        gates.assert_gates(o, ref, what=f"{how}, {what}")
+        # lse up to 1000s here: fp32 roundings of the scores (2^-24 of |q||k| summed over d) and of lse
+        # itself, against the absolute bound that holds for lse of order 10
+        gates.assert_lse(l, ref_lse, what=f"{how}, {what}", tol=max(gates.LSE_ABS, 4 * 2.0 ** -23 * float(np.abs(ref_lse).max())))
+    assert plan.device_error() == 0 and pplan.device_error() == 0
 
 
 def test_prefill_tiled_nonfinite_instruction_value(fa):
