@@ -399,6 +399,31 @@ def test_lse_merge_stage(fa, d):
     np.testing.assert_allclose(got_lse[fin], ref_lse[fin], rtol=1e-6, atol=1e-5)
 
 
+@pytest.mark.parametrize("d,R,P", [(128, 1, 1), (128, 7, 8), (64, 17, 8), (128, 9, 9), (128, 2047, 16), (128, 2049, 16),
+                                   (64, 2050, 9), (64, 2048, 32), (128, 2048, 33), (64, 3, 0)])
+def test_lse_merge_rows_per_block(fa, d, R, P):
+    """Both explicit-mode merges at the edges of their rule (8 and 32 parts, 2048 rows) and of a block's
+    rows (8 at d 128, 16 at d 64), with empty parts whose o is NaN (never read into a row) and a row
+    without any key."""
+    rng = np.random.default_rng(1000 * P + R)
+    o = rng.standard_normal((P, R, d)).astype(np.float32)
+    l = rng.uniform(-30, 30, (P, R)).astype(np.float32)
+    l[rng.random((P, R)) < 0.3] = -np.inf
+    l[:, R // 2] = -np.inf
+    empty = np.isneginf(l)
+    out = torch.full((R, d), float("nan"), device="cuda")
+    lse = torch.full((R,), float("nan"), device="cuda")
+    fa.lse_merge(torch.from_numpy(np.where(empty[..., None], np.float32("nan"), o)).cuda(), torch.from_numpy(l).cuda(), out, lse)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.lse_merge(np.where(empty[..., None], 0, o).transpose(1, 0, 2).astype(np.float64), l.T.astype(np.float64))
+    # fp32 sums of at most 33 terms and a hardware exp2 / reciprocal of a few ulp: under 1e-5 of |o| <= 5
+    np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=1e-5, atol=1e-5)
+    got = lse.cpu().numpy()
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref_lse)) and np.isneginf(got[R // 2])
+    fin = np.isfinite(ref_lse)
+    np.testing.assert_allclose(got[fin], ref_lse[fin], rtol=1e-6, atol=1e-5)
+
+
 def _small_paged(headroom=0, seed=90):
     return W.make(W.CONFIGS["paged"].replace(n_tasks=5, prefix_range=(1, 3000), suffix_range=(0, 400),
                                              page_headroom=headroom, seed=seed))
