@@ -23,7 +23,7 @@ struct fka_plan {
     int32_t prefill_n = 0;     // instruction prefill plan: tokens per branch (sequences are b * n + t)
     int32_t n_branches = 0;    // instruction prefill plan: branches
     int32_t prefill_groups = 1; // instruction prefill plan: units per block
-    // instruction prefill on the tiled kernel (head_dim 128): 32-row units per KV head, blocks of
+    // instruction prefill on the tiled kernel: 32-row units per KV head, blocks of
     // eight units, key ranges, whole prefix tiles of 64 keys
     bool prefill_tiles = false;
     int32_t tile_units = 0, tile_unit_groups = 0, tile_ranges = 0, tile_prefix = 0;
@@ -377,7 +377,7 @@ fka_status run_decode(const fka_plan *p, const fka::AttnArgs &a, const int32_t *
     return ok();
 }
 
-// The instruction prefill's two launches: the tiled kernel (head_dim 128) with the merge in its
+// The instruction prefill's two launches: the tiled kernel with the merge in its
 // explicit mode (every row merges its ranges' partials), or the partial kernel's prefill
 // instantiation with the plan-mode merge.
 fka_status run_prefill(const fka_plan *p, const fka::AttnArgs &a, float *out, float *out_lse, hipStream_t s)
@@ -413,7 +413,7 @@ fka_status run_prefill(const fka_plan *p, const fka::AttnArgs &a, float *out, fl
         t.ranges = p->tile_ranges;
         t.prefix_tiles = p->tile_prefix;
         t.scale_log2 = p->scale * 1.4426950408889634f;
-        e = fka::launch_prefill_tiles(t, p->n_blocks, s);
+        e = fka::launch_prefill_tiles(t, p->n_blocks, p->d, s);
         if (e != hipSuccess) return hip_fail(e, "prefill kernel launch");
         fka::MergeArgs m{};
         m.part_o = p->part_o;
@@ -471,6 +471,26 @@ struct PrefillLayout {
     int32_t n_pool_pages;
 };
 
+// Whether an instruction prefill of `rows` query rows per KV head over `keys` prefix keys (summed over
+// the KV heads) takes the tiled kernel or the partial kernel's prefill instantiation.  A tiled call
+// has the longer fixed part (a block's start, two phases per tile, a partial per range: about 25 us
+// from five units on, 19 below, against 15), the instantiation the longer one per unit and key (it
+// loads every key again for each unit of 32 rows).  Measured, us tiled / instantiation, 8 KV heads:
+//   d 128, 8 units: 2000 keys 28.7 / 22.9, 5000 32.4 / 31.9, 14000 40 / 56, 32768 63 / 121
+//          4 units: 2000 20.0 / 17.9, 5000 24.4 / 22.1, 14000 29.1 / 30.7, 32768 44.5 / 57.8
+//          1 unit: 600 15.3 / 17.0, 5000 18.0 / 18.4, 14000 23.6 / 21.3, 32768 37.7 / 34.5
+//   d 64,  8 units: 2000 21.4 / 21.2, 32768 43 / 67; 2 units: 600 13.4 / 18.6, 14000 21.2 / 21.5,
+//          32768 29.3 / 26.2; 1 unit: 2000 14.3 / 13.9, 14000 19.3 / 16.5
+// (2 and 4 KV heads cross at the same products).  From eight units on the tiled kernel throughout.
+bool use_prefill_tiles(int head_dim, int64_t rows, int64_t keys)
+{
+    const int64_t units = (rows + fka::prefill_tiles_unit_rows() - 1) / fka::prefill_tiles_unit_rows();
+    if (rows >= (int64_t)fka::prefill_tiles_waves() * fka::prefill_tiles_unit_rows()) return true;
+    if (head_dim == 64) return units >= 3 || keys <= 40000 * units;
+    if (units == 1) return keys <= 40000;
+    return units >= 3 && units * keys >= (units <= 4 ? 140000 : 300000);
+}
+
 fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t Lp, int32_t max_suffix_len,
                           int32_t blocks, const PrefillLayout &lay, fka_plan **out)
 {
@@ -511,14 +531,11 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
     int cus = 0;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device)) != hipSuccess)
         return bail(hip_fail(e, "hipDeviceGetAttribute"));
-    // The tiled kernel when each KV head has at least one block's worth of units (eight of 32
-    // rows); fewer rows than that leave most of a block's waves idle there, and the partial kernel's
-    // prefill instantiation, which spreads each unit's keys over four waves, is faster.
     const int tile_rows = fka::prefill_tiles_unit_rows(), tile_waves = fka::prefill_tiles_waves();
-    if (p->d == 128 && S * G >= (int64_t)tile_waves * tile_rows) {
+    if (use_prefill_tiles(p->d, S * G, (int64_t)Lp * p->Hkv)) {
         // The tiled kernel: units of 32 consecutive rows of a KV head, eight per block (one per
         // wave) over one of R ranges of the keys, R such that the blocks fill the device.
-        const int per_cu = fka::prefill_tiles_blocks_per_cu(lay.paged);
+        const int per_cu = fka::prefill_tiles_blocks_per_cu(p->d, lay.paged);
         if (per_cu <= 0) return bail(fail(FKA_ERR_HIP, "occupancy query of the prefill kernel failed"));
         const int64_t rows_head = S * G;
         const int32_t U = (int32_t)ceil_div(rows_head, tile_rows);
@@ -527,7 +544,10 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
         const int64_t base = (int64_t)p->Hkv * UG;
         const int64_t want = blocks > 0 ? blocks : (int64_t)cus * per_cu;
         int64_t R = std::max<int64_t>(1, want / base);
-        R = std::min<int64_t>(R, std::max(1, PT));
+        // at least three tiles to a range: a range costs each row a partial (written, and read by the
+        // merge) and each block a start (measured with 128 tiles, 2 KV heads: 240 rows 26.3 us in 43
+        // ranges, 27.0 in 64, 29.4 in 128, 27.4 in 32; 80 rows 17.3, 17.7, 19.4 and 20.2)
+        R = std::min<int64_t>(R, std::max(1, PT / 3));
         // the partials of one range: S Hq rows of d floats; the ranges together stay below 256 MiB
         const int64_t range_bytes = S * p->Hq * (int64_t)p->d * 4;
         R = std::max<int64_t>(1, std::min<int64_t>(R, ((int64_t)256 << 20) / range_bytes));

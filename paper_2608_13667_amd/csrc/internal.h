@@ -232,7 +232,7 @@ struct ScatterArgs {
     int32_t *err;                   // nullable
 };
 
-// Instruction prefill as a tiled multi-query kernel (prefill.hip, head_dim 128).  Rows of KV head g
+// Instruction prefill as a tiled multi-query kernel (prefill.hip).  Rows of KV head g
 // are cut into units of 32 (row i: query head g G + i mod G of virtual sequence i / G, where
 // sequence s = b n + t is instruction token t of branch b); block vb takes KV head vb mod Hkv,
 // unit group k = (vb / Hkv) mod unit_groups (units [floor(k U / UG), floor((k + 1) U / UG)), at
@@ -284,12 +284,12 @@ int prefill_max_rows(int head_dim, int group);
 hipError_t launch_prefill(const AttnArgs &a, int n_blocks, int head_dim, int row_tiles, hipStream_t s);
 int prefill_blocks_per_cu(int head_dim, int row_tiles, bool paged);
 hipError_t launch_merge(const MergeArgs &a, int head_dim, hipStream_t s);
-// The tiled instruction prefill (head_dim 128): query rows per unit (one wave each), waves (and
+// The tiled instruction prefill: query rows per unit (one wave each), waves (and
 // so units) per block, resident blocks per compute unit, and the launch.
 int prefill_tiles_unit_rows();
 int prefill_tiles_waves();
-int prefill_tiles_blocks_per_cu(bool paged);
-hipError_t launch_prefill_tiles(const PrefillArgs &a, int n_blocks, hipStream_t s);
+int prefill_tiles_blocks_per_cu(int head_dim, bool paged);
+hipError_t launch_prefill_tiles(const PrefillArgs &a, int n_blocks, int head_dim, hipStream_t s);
 hipError_t launch_append(const AppendArgs &a, int n_seqs, hipStream_t s);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
 hipError_t launch_scatter(const ScatterArgs &a, hipStream_t s);

@@ -943,22 +943,36 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 int prefill_tiles_unit_rows() { return 32; }
 int prefill_tiles_waves() { return NW; }
 
-int prefill_tiles_blocks_per_cu(bool paged)
+int prefill_tiles_blocks_per_cu(int head_dim, bool paged)
 {
+    const void *f = nullptr;
+    if (head_dim == 128)
+        f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<128, true>)
+                  : reinterpret_cast<const void *>(&prefill_tiles_kernel<128, false>);
+    else if (head_dim == 64)
+        f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<64, true>)
+                  : reinterpret_cast<const void *>(&prefill_tiles_kernel<64, false>);
     int n = 0;
-    const void *f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<128, true>)
-                          : reinterpret_cast<const void *>(&prefill_tiles_kernel<128, false>);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * NW, 0) != hipSuccess) return 0;
+    if (!f || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * NW, 0) != hipSuccess) return 0;
     return n;
 }
 
-hipError_t launch_prefill_tiles(const PrefillArgs &a, int n_blocks, hipStream_t s)
+hipError_t launch_prefill_tiles(const PrefillArgs &a, int n_blocks, int head_dim, hipStream_t s)
 {
     if (n_blocks <= 0) return hipSuccess;
-    if (a.paged)
-        prefill_tiles_kernel<128, true><<<n_blocks, 64 * NW, 0, s>>>(a);
-    else
-        prefill_tiles_kernel<128, false><<<n_blocks, 64 * NW, 0, s>>>(a);
+    if (head_dim == 128) {
+        if (a.paged)
+            prefill_tiles_kernel<128, true><<<n_blocks, 64 * NW, 0, s>>>(a);
+        else
+            prefill_tiles_kernel<128, false><<<n_blocks, 64 * NW, 0, s>>>(a);
+    } else if (head_dim == 64) {
+        if (a.paged)
+            prefill_tiles_kernel<64, true><<<n_blocks, 64 * NW, 0, s>>>(a);
+        else
+            prefill_tiles_kernel<64, false><<<n_blocks, 64 * NW, 0, s>>>(a);
+    } else {
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -250,6 +250,36 @@ def test_prefill_tiled_moving_reference(fa, how):
     assert plan.device_error() == 0 and pplan.device_error() == 0
 
 
+@pytest.mark.parametrize("c,tiled", [
+    (dict(head_dim=128, n_kv_heads=2, n_q_heads=2, n_branches=4, n=8, prefix_len=1100), True),     # 1 unit, few keys
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=8, n_branches=3, n=11, prefix_len=700), False),    # 2 units
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=2950), True),  # 3 units, 47200 keys
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=2900), False),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4700), True),  # 8 units, 254 rows
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4600), False),
+    (dict(head_dim=64, n_kv_heads=8, n_q_heads=8, n_branches=2, n=16, prefix_len=4999), True),     # 1 unit, 39992 keys
+    (dict(head_dim=64, n_kv_heads=8, n_q_heads=8, n_branches=2, n=16, prefix_len=5001), False),
+    (dict(head_dim=64, n_kv_heads=2, n_q_heads=10, n_branches=3, n=5, prefix_len=63), True),       # 3 units, no whole tile
+    (dict(head_dim=64, n_kv_heads=4, n_q_heads=28, n_branches=2, n=37, prefix_len=833), True),     # 17 units
+], ids=lambda x: x if isinstance(x, bool) else f"d{x['head_dim']}-kv{x['n_kv_heads']}-n{x['n']}-p{x['prefix_len']}")
+def test_prefill_kernel_choice(fa, c, tiled):
+    """Both prefill kernels at the lines of the rule that chooses between them (units of 32 query rows
+    per KV head, prefix keys over all KV heads), contiguous and paged, every row checked."""
+    n = c["n"]
+    w = W.make(W.CONFIGS["mid"].replace(head_dim=c["head_dim"], n_kv_heads=c["n_kv_heads"], n_q_heads=c["n_q_heads"],
+                                        n_branches=c["n_branches"], prefix_len=c["prefix_len"], suffix_range=(0, 30),
+                                        steps=n, seed=2767))
+    q, sk, sv = _instruction(w, n)
+    ref, ref_lse = _reference(w, n, q, sk, sv)
+    plan, out, lse = _run(fa, w, n, q, sk, sv)
+    pplan, pout, plse = _run_paged(fa, w, n, q, sk, sv, seed=2768)
+    for what, p, o, l in (("contiguous", plan, out, lse), ("paged", pplan, pout, plse)):
+        assert (p.info().units_per_block == 8) == tiled
+        gates.assert_gates(o, ref, what=f"{c}, {what}")
+        gates.assert_lse(l, ref_lse, what=f"{c}, {what}")
+        assert p.device_error() == 0
+
+
 def test_prefill_tiled_nonfinite_instruction_value(fa):
     """A NaN in the value of instruction token 17 of branch 1 (KV head 1) reaches exactly the rows
     that attend to it: branch 1's tokens 17.. on that KV head's query heads.  Its earlier tokens and
