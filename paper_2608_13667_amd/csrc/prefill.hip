@@ -304,7 +304,7 @@ struct MatrixPlan {
 // power limit, registers only, 1370 TFLOP/s against 2000; here the clock fell from 2.4 to 2.0 GHz
 // and the call took as long.)
 template <int HD, bool PAGED>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void prefill_tiles_kernel(PrefillArgs a)
+__device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
 {
     constexpr int ROWB = HD * 2;            // bytes per key row
     constexpr int CPR = HD / 8;             // 16-byte chunks per key row
@@ -938,6 +938,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 }
 
+template <bool PAGED>  // head_dim 128
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void prefill_tiles_kernel(PrefillArgs a)
+{
+    prefill_tiles<128, PAGED>(a);
+}
+
+template <bool PAGED>  // head_dim 64
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void prefill_tiles_d64_kernel(PrefillArgs a)
+{
+    prefill_tiles<64, PAGED>(a);
+}
+
 }  // namespace
 
 int prefill_tiles_unit_rows() { return 32; }
@@ -947,11 +959,11 @@ int prefill_tiles_blocks_per_cu(int head_dim, bool paged)
 {
     const void *f = nullptr;
     if (head_dim == 128)
-        f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<128, true>)
-                  : reinterpret_cast<const void *>(&prefill_tiles_kernel<128, false>);
+        f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<true>)
+                  : reinterpret_cast<const void *>(&prefill_tiles_kernel<false>);
     else if (head_dim == 64)
-        f = paged ? reinterpret_cast<const void *>(&prefill_tiles_kernel<64, true>)
-                  : reinterpret_cast<const void *>(&prefill_tiles_kernel<64, false>);
+        f = paged ? reinterpret_cast<const void *>(&prefill_tiles_d64_kernel<true>)
+                  : reinterpret_cast<const void *>(&prefill_tiles_d64_kernel<false>);
     int n = 0;
     if (!f || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * NW, 0) != hipSuccess) return 0;
     return n;
@@ -962,14 +974,14 @@ hipError_t launch_prefill_tiles(const PrefillArgs &a, int n_blocks, int head_dim
     if (n_blocks <= 0) return hipSuccess;
     if (head_dim == 128) {
         if (a.paged)
-            prefill_tiles_kernel<128, true><<<n_blocks, 64 * NW, 0, s>>>(a);
+            prefill_tiles_kernel<true><<<n_blocks, 64 * NW, 0, s>>>(a);
         else
-            prefill_tiles_kernel<128, false><<<n_blocks, 64 * NW, 0, s>>>(a);
+            prefill_tiles_kernel<false><<<n_blocks, 64 * NW, 0, s>>>(a);
     } else if (head_dim == 64) {
         if (a.paged)
-            prefill_tiles_kernel<64, true><<<n_blocks, 64 * NW, 0, s>>>(a);
+            prefill_tiles_d64_kernel<true><<<n_blocks, 64 * NW, 0, s>>>(a);
         else
-            prefill_tiles_kernel<64, false><<<n_blocks, 64 * NW, 0, s>>>(a);
+            prefill_tiles_d64_kernel<false><<<n_blocks, 64 * NW, 0, s>>>(a);
     } else {
         return hipErrorInvalidValue;
     }

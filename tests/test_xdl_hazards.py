@@ -45,3 +45,18 @@ def test_every_xdl_result_read_is_padded_in_the_prefill_kernel():
         pairs = X.scan(asm, k)
         assert pairs, k
         assert min(p[0] for p in pairs) >= X.MIN_WAIT, (k, sorted(pairs)[:3])
+
+
+@pytest.mark.slow
+def test_every_xdl_result_read_is_padded_in_the_d64_prefill_kernel():
+    hipcc = next((c for c in ("/opt/rocm/bin/hipcc", shutil.which("hipcc")) if c and os.path.exists(c)), None)
+    if hipcc is None:
+        pytest.skip("hipcc not found")
+    with tempfile.TemporaryDirectory() as d:
+        asm = X.compile_asm(hipcc, os.path.join(ROOT, "paper_2608_13667_amd", "csrc", "prefill.hip"),
+                            os.path.join(ROOT, "include"), os.path.join(d, "prefill.s"))
+    ks = X.kernels(asm, "prefill_tiles_d64_kernel")
+    assert len(ks) == 2
+    for k in ks:
+        pairs = X.scan(asm, k)
+        assert pairs and min(p[0] for p in pairs) >= X.MIN_WAIT, (k, sorted(pairs)[:3])
