@@ -303,6 +303,26 @@ fka_status check_contig(const fka_heads *heads, const fka_contig_desc *desc)
     return FKA_OK;
 }
 
+// The reciprocals of a static split of whole blocks, or bpi = 0.  With W workers per item and b up to
+// the item's slices at the longest suffixes, the products they are used on stay below 2^32:
+// b W (a list's share per worker), W^3 (j r with j <= W, r < W, times W), blocks x bpi.
+fka::EvenSplit even_split_of(const fka_plan *p)
+{
+    fka::EvenSplit e{};
+    const int64_t blocks = (int64_t)p->n_blocks * p->rounds;
+    if (!p->static_split || p->prefill_n || blocks % p->Hkv != 0) return e;
+    const int64_t bpi = blocks / p->Hkv, W = bpi * p->waves;
+    const int64_t slices = p->ps_total + (int64_t)p->n_seqs * fka::slices_of(p->max_suffix_len);
+    if (W > 1024 || slices * W >= ((int64_t)1 << 31) || blocks * bpi >= ((int64_t)1 << 31)) return e;
+    e.bpi = (int32_t)bpi;
+    e.bpi_magic = fka::magic_of((uint32_t)bpi);
+    e.w_magic = fka::magic_of((uint32_t)W);
+    e.rows_magic = fka::magic_of((uint32_t)p->slot_rows);  // pieces of a row x rows stay below 2^16
+    e.pre_q = p->ps_total / (int32_t)W;
+    e.pre_r = p->ps_total % (int32_t)W;
+    return e;
+}
+
 fka::AttnArgs attn_args(const fka_plan *p)
 {
     fka::AttnArgs a{};
@@ -318,6 +338,8 @@ fka::AttnArgs attn_args(const fka_plan *p)
     a.n_q_heads = p->Hq;
     a.n_kv_heads = p->Hkv;
     a.group = p->G;
+    a.group_magic = fka::magic_of((uint32_t)p->G);
+    a.even = even_split_of(p);
     a.scale_log2 = p->scale * 1.4426950408889634f;
     a.part_o = p->part_o;
     a.part_lse = p->part_lse;
@@ -351,6 +373,8 @@ fka::MergeArgs merge_args(const fka_plan *p, const int32_t *suffix_len, float *o
     m.lens = p->d_lens;
     m.slot_rows = p->slot_rows;
     m.n_slots = p->n_slots;
+    m.even_bpi = even_split_of(p).bpi;
+    m.group_magic = fka::magic_of((uint32_t)p->G);
     m.waves = p->waves;
     m.n_workers = p->n_blocks * p->rounds * p->waves;
     m.suffix_len = const_cast<int32_t *>(suffix_len);  // only a fused step writes it

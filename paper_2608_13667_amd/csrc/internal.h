@@ -113,6 +113,32 @@ __host__ __device__ inline int32_t suf_split(int32_t j, int32_t W, int32_t P, in
     return mul_div(j, S, W);
 }
 
+// floor(x / d) for x d < 2^32 by a multiplication with magic = ceil(2^32 / d) (unused for d = 1): a
+// division in device code is a chain of some 30 instructions, and the split's stand in front of the
+// first loads.
+__host__ __device__ inline uint32_t magic_of(uint32_t d) { return d <= 1 ? 0 : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+__host__ __device__ inline int32_t div_magic(int32_t x, int32_t d, uint32_t magic)
+{
+    return d == 1 ? x : (int32_t)(((uint64_t)(uint32_t)x * magic) >> 32);
+}
+
+// A static split of whole blocks: the blocks are a multiple of the KV heads, so item g owns blocks
+// [g bpi, (g + 1) bpi), W = bpi x waves workers.  bpi = 0: not such a split, or sizes past what the
+// multiplications are exact for (see even_split_of in api.hip).
+struct EvenSplit {
+    int32_t bpi;
+    uint32_t bpi_magic;  // of bpi
+    uint32_t w_magic;    // of W
+    uint32_t rows_magic; // of the item's rows
+    int32_t pre_q, pre_r;  // prefix slices / W, remainder
+};
+
+// floor(j b / W) with b = q W + r (0 <= j <= W): pre_split and suf_split of an even split.
+__host__ __device__ inline int32_t even_split(int32_t j, int32_t q, int32_t r, uint32_t w_magic)
+{
+    return j * q + (int32_t)(((uint64_t)(uint32_t)(j * r) * w_magic) >> 32);
+}
+
 struct AttnArgs {
     const UnitRec *units;  // [n_units]
     int32_t n_units;
@@ -139,6 +165,8 @@ struct AttnArgs {
     int32_t n_q_heads;
     int32_t n_kv_heads;
     int32_t group;
+    uint32_t group_magic;  // of group
+    EvenSplit even;        // bpi > 0: a static split of whole blocks
     float scale_log2;  // softmax scale * log2(e)
     float *part_o;     // [slots][slot_rows][d]
     float *part_lse;   // [slots][slot_rows]
@@ -168,6 +196,8 @@ struct MergeArgs {
     int32_t slot_rows;
     int32_t n_slots;           // records pointing outside [0, n_slots * slot_rows) are not followed
     int32_t *err;
+    int32_t even_bpi;   // static split of whole blocks: blocks per item, else 0
+    uint32_t group_magic;  // of group
     int32_t waves;      // NW: workers per virtual block
     int32_t n_workers;  // NV
     // fused step: the token in k_new / v_new (not yet in the cache) joins each row as one

@@ -15,7 +15,8 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
     __shared__ MergeLds<HD> lds;
     constexpr int APP = HD / 8;  // 16-byte chunks of one K/V row
     const int tid = threadIdx.x;
-    const int row = blockIdx.x;
+    // plan mode: a block per (query head, sequence), so that neither needs a division
+    const int row = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
 
     // Everything this block reads is requested together: under a static split the row's parts
     // (their slots follow from the plan) with, in a fused step, the length, q and the appended
@@ -28,11 +29,14 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
     int seq = 0;
     uint4 app_k = {0, 0, 0, 0}, app_v = {0, 0, 0, 0};  // fused step, block (s, 0): the token to store
     if (a.plan) {
-        seq = row / a.n_q_heads;
-        const int h = row % a.n_q_heads;
-        const int g = h / a.group;
+        seq = blockIdx.y;
+        const int h = blockIdx.x;
+        const int g = div_magic(h, a.group, a.group_magic);
         m.p_step = a.slot_rows;
-        if (a.static_split) {
+        if (a.even_bpi > 0) {  // item g's blocks g bpi .. write slots vb + g
+            m.n = a.even_bpi;
+            m.p_first = (int64_t)(g * a.even_bpi + g) * a.slot_rows + (int64_t)seq * a.group + (h - g * a.group);
+        } else if (a.static_split) {
             // item g owns workers [floor(g NV / Hkv), floor((g+1) NV / Hkv)); its blocks write
             // their partials to slots vb + g; the one unit starts at sequence 0
             const int ws0 = static_start(g, a.n_workers, a.n_kv_heads);
@@ -74,7 +78,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
     // Fused step: block (s, head 0) stores the token sequence s appended (already attended
     // to from k_new / v_new) and advances suffix_len[s].  No block of this kernel reads the
     // suffix cache or suffix_len (the lengths come from the partial kernel), so nothing races.
-    if (!a.step_mode || row % a.n_q_heads != 0) return;
+    if (!a.step_mode || blockIdx.x != 0) return;
     const int L = m.L;
     bool ok = L < a.max_suffix_len;
     int page = 0;
@@ -316,7 +320,7 @@ bool several_rows_per_block(const MergeArgs &a)
 hipError_t launch_merge(const MergeArgs &a, int head_dim, hipStream_t s)
 {
     if (a.rows <= 0) return hipSuccess;
-    const dim3 grid(a.rows), block(256);
+    const dim3 grid = a.plan ? dim3(a.n_q_heads, a.rows / a.n_q_heads) : dim3(a.rows), block(256);
     if (several_rows_per_block(a)) {
         const int per_block = 1024 / head_dim;
         const dim3 g((a.rows + per_block - 1) / per_block);

@@ -10,6 +10,8 @@
 // (it is stored into the cache after every block of the step has read the lengths).
 #pragma once
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace fka {
@@ -34,6 +36,24 @@ struct RowMerge {
     float *out_row;         // fp32 [HD]
     float *out_lse;         // fp32, nullable
 };
+
+// Sum over the wave in vector-ALU steps (a shuffle is an LDS round trip): the halves, the 16-lane
+// rows, then within a row.
+__device__ inline float wave_sum(float x)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    auto ror = [](float v, auto n) {  // the row rotated by n lanes (DPP row_ror)
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + decltype(n)::value, 0xf, 0xf, false));
+    };
+    x += ror(x, std::integral_constant<int, 8>{});
+    x += ror(x, std::integral_constant<int, 4>{});
+    x += ror(x, std::integral_constant<int, 2>{});
+    x += ror(x, std::integral_constant<int, 1>{});
+    return x;
+}
 
 // LDS the routine uses.
 template <int HD>
@@ -103,8 +123,7 @@ __device__ inline void merge_row(const RowMerge &m, MergeLds<HD> &lds)
         }
         lds.acc[slice][chunk] = acc;
         if (m.step && wave == 0) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) dot += __shfl_xor(dot, off);
+            dot = wave_sum(dot);
             if (lane == 0) lds.lse_new = dot * m.scale;
         }
     }

@@ -298,6 +298,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
     const int w_lo = vb * NW;
     const int max_len = a.max_suffix_len;
     const bool static_split = a.static_split != 0;
+    const bool even = !PREFILL && a.even.bpi > 0;  // a static split of whole blocks (EvenSplit)
 
     // ---- this wave's item, its unit and the group (uniform)
     int item = -1, unit = 0, Wi = 1, jg0 = 0, jg1 = 0, wa = wave, we = wave + 1;
@@ -307,18 +308,33 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
         // the item and group follow from the plan; the lengths are requested now and waited for
         // only after the first prefix loads are issued
         if (lane < N) lraw = a.suffix_len[lane];
-        const int w = w_lo + wave;
-        item = static_item(w, NV, Hkv);
-        const int ws0 = static_start(item, NV, Hkv), ws1 = static_start(item + 1, NV, Hkv);
-        const int lo = max(ws0, w_lo), hi = min(ws1, w_lo + NW);
-        Wi = ws1 - ws0;
-        jg0 = lo - ws0;
-        jg1 = hi - ws0;
-        wa = lo - w_lo;
-        we = hi - w_lo;
         nseq = N;
         plen = a.prefix_len;
-        if (wave == 0) {  // the block's groups, in wave order (read after the combine barrier)
+        if (even) {
+            // whole blocks per item, in multiplications by the host's reciprocals
+            item = div_magic(vb, a.even.bpi, a.even.bpi_magic);
+            const int k = vb - item * a.even.bpi;
+            Wi = a.even.bpi * NW;
+            jg0 = k * NW;
+            jg1 = jg0 + NW;
+            wa = 0;
+            we = NW;
+            if (tid == 0) {
+                *reinterpret_cast<int4 *>(&s_grp[0][0]) = int4{0, NW, N * G, item};
+                s_ngrp = 1;
+            }
+        } else {
+            const int w = w_lo + wave;
+            item = static_item(w, NV, Hkv);
+            const int ws0 = static_start(item, NV, Hkv), ws1 = static_start(item + 1, NV, Hkv);
+            const int lo = max(ws0, w_lo), hi = min(ws1, w_lo + NW);
+            Wi = ws1 - ws0;
+            jg0 = lo - ws0;
+            jg1 = hi - ws0;
+            wa = lo - w_lo;
+            we = hi - w_lo;
+        }
+        if (!even && wave == 0) {  // the block's groups, in wave order (read after the combine barrier)
             const int wl = lane < NW ? lane : 0;
             const int it = static_item(w_lo + wl, NV, Hkv);
             const bool lead = lane < NW && (wl == 0 || static_item(w_lo + wl - 1, NV, Hkv) != it);
@@ -504,7 +520,16 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
     const int Ps = slices_of(plen);
     // the group's prefix slices [pa, pa + np) (known from the plan), its waves and this wave's
     // place among them: wave j of the group's gn waves takes list entries j, j + gn, ...
-    const int pa = uni(pre_split(jg0, Wi, Ps)), np = uni(pre_split(jg1, Wi, Ps) - pa);
+    int pa, np;
+    if (even) {
+        pa = even_split(jg0, a.even.pre_q, a.even.pre_r, a.even.w_magic);
+        np = even_split(jg1, a.even.pre_q, a.even.pre_r, a.even.w_magic) - pa;
+    } else {
+        pa = pre_split(jg0, Wi, Ps);
+        np = pre_split(jg1, Wi, Ps) - pa;
+    }
+    pa = uni(pa);
+    np = uni(np);
     const int gn = uni(we - wa), gw = uni(wave - wa);
     // suffix part (set once the lengths are known): lane i holds the clamped length of the
     // unit's sequence i and the inclusive scan of the sequences' slice counts
@@ -633,7 +658,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
 #pragma unroll
         for (int c = 0; c < NC; ++c) qb[t][c] = bf16x8{};
         if (item >= 0 && r < rows) {
-            const int seq = seq0 + r / G, h = kvh * G + r % G;
+            const int rq = div_magic(r, G, a.group_magic);
+            const int seq = seq0 + rq, h = kvh * G + r - rq * G;
             const uint16_t *qp = a.q + ((size_t)seq * a.n_q_heads + h) * HD + 8 * q4;
 #pragma unroll
             for (int c = 0; c < NC; ++c) qb[t][c] = *reinterpret_cast<const bf16x8 *>(qp + 32 * c);
@@ -675,8 +701,16 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
     }
     if (item >= 0) {
         const int S = __builtin_amdgcn_readlane(csv, 63);
-        sa = uni(suf_split(jg0, Wi, Ps, S));
-        nlist = uni(np + suf_split(jg1, Wi, Ps, S) - sa);
+        if (even) {
+            // suf_split: of P + S less the prefix's share when S >= W, of S otherwise
+            const int b = S >= Wi ? Ps + S : S, bq = div_magic(b, Wi, a.even.w_magic), br = b - bq * Wi;
+            const int s0 = even_split(jg0, bq, br, a.even.w_magic), s1 = even_split(jg1, bq, br, a.even.w_magic);
+            sa = uni(S >= Wi ? s0 - pa : s0);
+            nlist = uni(np + (S >= Wi ? s1 - (pa + np) : s1) - sa);
+        } else {
+            sa = uni(suf_split(jg0, Wi, Ps, S));
+            nlist = uni(np + suf_split(jg1, Wi, Ps, S) - sa);
+        }
     }
     // the query rows have arrived when only the first slice's loads are in flight (stated here,
     // so the loop does not wait for everything on its first entry)
@@ -896,6 +930,57 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
     auto stg_off = [&](int r, int c4) {  // float offset of chunk c4 (4 floats) of row r in a tile
         return r * HD + 4 * (c4 ^ (r & 15));
     };
+    // unit cu of row `row` from the waves [lw, ge) of its group, written to slot slot_c
+    auto piece = [&](int pass, int row, int cu, int lw, int ge, bool whole, int slot_c) __attribute__((always_inline)) {
+        const int t = row >> 4, tt = t - TPP * pass, r = row & 15;
+        // a wave of the group that saw no keys has max -inf, weight 0 and a zero
+        // accumulator; waves outside the group are never read (their staging may
+        // hold another item's NaN)
+        float M = -INFINITY, L = 0.f;
+        f32x4 o[UQ];
+#pragma unroll
+        for (int q = 0; q < UQ; ++q) o[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (whole) {
+            float mw[NW], lw_[NW];
+            f32x4 v[NW][UQ];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                mw[w] = red_m[t][r][w];
+                lw_[w] = red_l[t][r][w];
+#pragma unroll
+                for (int q = 0; q < UQ; ++q)
+                    v[w][q] = *reinterpret_cast<const f32x4 *>(&stg(w, tt)[stg_off(r, UQ * cu + q)]);
+            }
+#pragma unroll
+            for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w]);
+            const float Mu = (M == -INFINITY) ? 0.f : M;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float wt = fast_exp2(mw[w] - Mu);  // 0 for max -inf
+                L = __builtin_fmaf(wt, lw_[w], L);
+#pragma unroll
+                for (int q = 0; q < UQ; ++q) o[q] += wt * v[w][q];
+            }
+        } else {
+            for (int w = lw; w < ge; ++w) M = fmaxf(M, red_m[t][r][w]);
+            const float Mu = (M == -INFINITY) ? 0.f : M;
+            for (int w = lw; w < ge; ++w) {
+                const float wt = fast_exp2(red_m[t][r][w] - Mu);
+                L = __builtin_fmaf(wt, red_l[t][r][w], L);
+#pragma unroll
+                for (int q = 0; q < UQ; ++q)
+                    o[q] += wt * *reinterpret_cast<const f32x4 *>(&stg(w, tt)[stg_off(r, UQ * cu + q)]);
+            }
+        }
+        // L == 0 only when the group saw no keys: its accumulators are zero and so is
+        // o; a NaN input keeps propagating
+        const float inv = (L == 0.f) ? 0.f : __builtin_amdgcn_rcpf(L);
+        const size_t so = (size_t)slot_c * a.slot_rows + row;
+        float *dst = a.part_o + so * HD + 4 * UQ * cu;
+#pragma unroll
+        for (int q = 0; q < UQ; ++q) *reinterpret_cast<f32x4 *>(dst + 4 * q) = o[q] * inv;
+        if (cu == 0) a.part_lse[so] = (L == 0.f) ? -INFINITY : (((M == -INFINITY) ? 0.f : M) + log2f(L)) * kLn2;
+    };
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
         if (pass > 0) lds_barrier();  // the previous pass has read the staging
@@ -911,6 +996,14 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             }
         }
         lds_barrier();  // also orders the group table (written by wave 0 before streaming)
+        if (NPASS == 1 && even) {  // one group of all waves, its rows and slot known: no table, no division
+            if (vb + item < a.n_slots)
+                for (int u = tid_c; u < rows * CHU; u += NTH) {
+                    const int cu = div_magic(u, rows, a.even.rows_magic);
+                    piece(0, u - cu * rows, cu, 0, NW, true, vb + item);
+                }
+            break;
+        }
         const int n_grp = min(s_ngrp, NW);
         for (int g = 0; g < n_grp; ++g) {
             const int4 gi = *reinterpret_cast<const int4 *>(&s_grp[g][0]);
@@ -922,57 +1015,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             if (slot_c >= a.n_slots || it < 0) continue;  // never store outside the workspace
             const int r0 = 16 * TPP * pass, r1 = min(gi.z, r0 + 16 * TPP);
             const bool whole = lw == 0 && ge == NW;  // the usual case: one group, all waves
-            for (int u = tid_c; u < (r1 - r0) * CHU; u += NTH) {
-                const int row = r0 + u % (r1 - r0), cu = u / (r1 - r0);
-                const int t = row >> 4, tt = t - TPP * pass, r = row & 15;
-                // a wave of the group that saw no keys has max -inf, weight 0 and a zero
-                // accumulator; waves outside the group are never read (their staging may
-                // hold another item's NaN)
-                float M = -INFINITY, L = 0.f;
-                f32x4 o[UQ];
-#pragma unroll
-                for (int q = 0; q < UQ; ++q) o[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (whole) {
-                    float mw[NW], lw_[NW];
-                    f32x4 v[NW][UQ];
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) {
-                        mw[w] = red_m[t][r][w];
-                        lw_[w] = red_l[t][r][w];
-#pragma unroll
-                        for (int q = 0; q < UQ; ++q)
-                            v[w][q] = *reinterpret_cast<const f32x4 *>(&stg(w, tt)[stg_off(r, UQ * cu + q)]);
-                    }
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w]);
-                    const float Mu = (M == -INFINITY) ? 0.f : M;
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) {
-                        const float wt = fast_exp2(mw[w] - Mu);  // 0 for max -inf
-                        L = __builtin_fmaf(wt, lw_[w], L);
-#pragma unroll
-                        for (int q = 0; q < UQ; ++q) o[q] += wt * v[w][q];
-                    }
-                } else {
-                    for (int w = lw; w < ge; ++w) M = fmaxf(M, red_m[t][r][w]);
-                    const float Mu = (M == -INFINITY) ? 0.f : M;
-                    for (int w = lw; w < ge; ++w) {
-                        const float wt = fast_exp2(red_m[t][r][w] - Mu);
-                        L = __builtin_fmaf(wt, red_l[t][r][w], L);
-#pragma unroll
-                        for (int q = 0; q < UQ; ++q)
-                            o[q] += wt * *reinterpret_cast<const f32x4 *>(&stg(w, tt)[stg_off(r, UQ * cu + q)]);
-                    }
-                }
-                // L == 0 only when the group saw no keys: its accumulators are zero and so is
-                // o; a NaN input keeps propagating
-                const float inv = (L == 0.f) ? 0.f : __builtin_amdgcn_rcpf(L);
-                const size_t so = (size_t)slot_c * a.slot_rows + row;
-                float *dst = a.part_o + so * HD + 4 * UQ * cu;
-#pragma unroll
-                for (int q = 0; q < UQ; ++q) *reinterpret_cast<f32x4 *>(dst + 4 * q) = o[q] * inv;
-                if (cu == 0) a.part_lse[so] = (L == 0.f) ? -INFINITY : (((M == -INFINITY) ? 0.f : M) + log2f(L)) * kLn2;
-            }
+            for (int u = tid_c; u < (r1 - r0) * CHU; u += NTH)
+                piece(pass, r0 + u % (r1 - r0), u / (r1 - r0), lw, ge, whole, slot_c);
         }
     }
     if (bad_page) atomicOr(a.err, kErrBadPage);

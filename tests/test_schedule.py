@@ -26,3 +26,13 @@ def test_schedule_invariants():
                        check=True, capture_output=True, cwd=d)
         r = subprocess.run([exe, "3000"], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+
+
+def test_even_split_matches_the_general_split():
+    with tempfile.TemporaryDirectory() as d:
+        exe = os.path.join(d, "even_split_check")
+        subprocess.run([_hipcc(), "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2608_13667_amd", "csrc"),
+                        os.path.join(ROOT, "tests", "native", "even_split_check.cpp"), "-o", exe],
+                       check=True, capture_output=True, cwd=d)
+        r = subprocess.run([exe, "3000"], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
