@@ -141,6 +141,12 @@ _KIND_DTYPES = {"bf16": torch.bfloat16, "i32": torch.int32, "f32": torch.float32
 def _p(t: Optional[torch.Tensor], kind: Optional[str] = None, device: Optional[int] = None):
     """Device pointer of a contiguous tensor on the plan's GPU, of the dtype the C ABI expects
     for this argument (bf16 q/K/V, int32 lengths and page tables, fp32 outputs)."""
+    # A plain tensor on the plan's GPU passes all the checks below in one expression and goes to the
+    # C call as a plain integer: 0.26 us against 0.35 with the checks in turn and a c_void_p made,
+    # ten times in a step.  Anything else, and every error, goes through the checks in turn.
+    if (type(t) is torch.Tensor and device is not None and t.is_cuda and t.get_device() == device
+            and t.dtype is _KIND_DTYPES.get(kind) and t.is_contiguous()):
+        return t.data_ptr()
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
@@ -156,8 +162,16 @@ def _p(t: Optional[torch.Tensor], kind: Optional[str] = None, device: Optional[i
     return _vp(t.data_ptr())
 
 
-def _stream(stream) -> _vp:
+# The current stream's handle without building a torch.cuda.Stream object (2.9 us of a call's 12);
+# torch.cuda.current_stream() where this torch does not have it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return _vp(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
