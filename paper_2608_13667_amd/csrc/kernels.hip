@@ -9,82 +9,37 @@
 namespace fka {
 namespace {
 
+// Where a row's parts are: kExplicit, every row merges parts 0 .. n_parts-1; a plan's split, even
+// (whole blocks per item), or the general static one or the proportional one.
+enum class MergeParts { kExplicit, kEven, kPlan };
+
+// Fused step, block (Hq, seq): stores the token the sequence appends (the merging blocks attend to it
+// from k_new / v_new) and advances suffix_len[seq].  No block of the merge reads the suffix
+// cache or suffix_len (the lengths come from the partial kernel), so nothing races.  A block of its own,
+// because the page look-up behind the length would make a merging block the launch's last.
 template <int HD>
-__global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
+__device__ inline void append_token(const MergeArgs &a, int seq)
 {
-    __shared__ MergeLds<HD> lds;
     constexpr int APP = HD / 8;  // 16-byte chunks of one K/V row
     const int tid = threadIdx.x;
-    // plan mode: a block per (query head, sequence), so that neither needs a division
-    const int row = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
-
-    // Everything this block reads is requested together: under a static split the row's parts
-    // (their slots follow from the plan) with, in a fused step, the length, q and the appended
-    // key and value; under a proportional split the row's record first.
-    RowMerge m{};
-    m.part_o = a.part_o;
-    m.part_lse = a.part_lse;
-    m.out_row = a.out + (size_t)row * HD;
-    m.out_lse = a.out_lse ? a.out_lse + row : nullptr;
-    int seq = 0;
-    uint4 app_k = {0, 0, 0, 0}, app_v = {0, 0, 0, 0};  // fused step, block (s, 0): the token to store
-    if (a.plan) {
-        seq = blockIdx.y;
-        const int h = blockIdx.x;
-        const int g = div_magic(h, a.group, a.group_magic);
-        m.p_step = a.slot_rows;
-        if (a.even_bpi > 0) {  // item g's blocks g bpi .. write slots vb + g
-            m.n = a.even_bpi;
-            m.p_first = (int64_t)(g * a.even_bpi + g) * a.slot_rows + (int64_t)seq * a.group + (h - g * a.group);
-        } else if (a.static_split) {
-            // item g owns workers [floor(g NV / Hkv), floor((g+1) NV / Hkv)); its blocks write
-            // their partials to slots vb + g; the one unit starts at sequence 0
-            const int ws0 = static_start(g, a.n_workers, a.n_kv_heads);
-            const int ws1 = static_start(g + 1, a.n_workers, a.n_kv_heads);
-            const int vb0 = ws0 / a.waves;
-            m.n = ws1 > ws0 ? (ws1 - 1) / a.waves - vb0 + 1 : 0;
-            m.p_first = (int64_t)(vb0 + g) * a.slot_rows + (int64_t)seq * a.group + (h - g * a.group);
-        } else {
-            const int2 rec = *reinterpret_cast<const int2 *>(a.rowrec + (size_t)row * kRowRec);
-            // a record that points outside the workspace (it cannot, unless the workspace was
-            // overwritten from outside) is dropped and flagged rather than followed
-            const int64_t lim = (int64_t)a.n_slots * a.slot_rows;
-            const bool ok = rec.y >= 0 && rec.x >= 0 && (int64_t)rec.x + (int64_t)max(rec.y - 1, 0) * a.slot_rows < lim;
-            if (!ok && tid == 0) atomicOr(a.err, kErrBadSchedule);
-            m.p_first = rec.x;
-            m.n = ok ? rec.y : 0;
-        }
-        if (a.step_mode) {
-            m.step = 1;
-            m.L = a.lens[seq];
-            m.max_len = a.max_suffix_len;
-            m.q_row = a.q + (size_t)row * HD;
-            m.k_row = a.k_new + ((size_t)seq * a.n_kv_heads + g) * HD;
-            m.v_row = a.v_new + ((size_t)seq * a.n_kv_heads + g) * HD;
-            m.scale = a.scale;
-            if (h == 0 && tid < a.n_kv_heads * APP) {
-                const size_t src = ((size_t)seq * a.n_kv_heads + tid / APP) * HD + 8 * (tid % APP);
-                app_k = *reinterpret_cast<const uint4 *>(a.k_new + src);
-                app_v = *reinterpret_cast<const uint4 *>(a.v_new + src);
-            }
-        }
-    } else {
-        m.n = a.n_parts;
-        m.p_first = row;
-        m.p_step = a.rows;
+    // the length, the prefix length and the first 256 chunks on their way together: as vector loads,
+    // since scalar ones would be waited for one by one
+    int zero = 0;
+    asm("" : "+v"(zero));
+    const int L = a.lens[seq + zero];
+    int plen = 0;
+    if (a.paged) plen = a.seq_prefix_len[seq + zero];
+    uint4 app_k = {0, 0, 0, 0}, app_v = {0, 0, 0, 0};
+    if (tid < a.n_kv_heads * APP) {
+        const size_t src = (size_t)seq * a.n_kv_heads * HD + 8 * tid;
+        app_k = *reinterpret_cast<const uint4 *>(a.k_new + src);
+        app_v = *reinterpret_cast<const uint4 *>(a.v_new + src);
     }
-    merge_row<HD>(m, lds);
-
-    // Fused step: block (s, head 0) stores the token sequence s appended (already attended
-    // to from k_new / v_new) and advances suffix_len[s].  No block of this kernel reads the
-    // suffix cache or suffix_len (the lengths come from the partial kernel), so nothing races.
-    if (!a.step_mode || blockIdx.x != 0) return;
-    const int L = m.L;
     bool ok = L < a.max_suffix_len;
     int page = 0;
-    if (ok && a.paged) {
-        const int pidx = (a.seq_prefix_len[seq] + kPageSize - 1) / kPageSize + L / kPageSize;
-        page = pidx < a.max_pages ? a.page_table[(size_t)seq * a.max_pages + pidx] : -1;
+    if (a.paged) {
+        const int pidx = (plen + kPageSize - 1) / kPageSize + L / kPageSize;
+        page = ok && pidx < a.max_pages ? a.page_table[(size_t)seq * a.max_pages + pidx] : -1;
         ok = page >= 0 && page < a.n_pool_pages;
     }
     if (ok) {
@@ -93,7 +48,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
             const size_t dst =
                 a.paged ? (((size_t)page * a.n_kv_heads + gg) * kPageSize + L % kPageSize) * HD + 8 * cc
                         : (((size_t)seq * a.n_kv_heads + gg) * a.suffix_cap + L) * HD + 8 * cc;
-            uint4 kk = app_k, vv = app_v;  // loaded at the start (the first 256 chunks)
+            uint4 kk = app_k, vv = app_v;
             if (c >= 256) {
                 const size_t src = ((size_t)seq * a.n_kv_heads + gg) * HD + 8 * cc;
                 kk = *reinterpret_cast<const uint4 *>(a.k_new + src);
@@ -109,6 +64,76 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
         else
             atomicOr(a.err, kErrAppendNoRoom);
     }
+}
+
+// One block per output row (plan modes: block (query head, sequence), so that neither needs a division).
+// A kernel for each way to find the parts and for the step, so that a launch reads its arguments at
+// once and waits for nothing in front of the part loads (one kernel for all of them waited for the
+// length, for q and the appended key, and for arguments read late: a fused step at 8k keys took 18.2 us, now 16.9,
+// at 512 keys and d 64 11.5, now 10.4).
+template <int HD, MergeParts PARTS, bool STEP>
+__global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
+{
+    __shared__ MergeLds<HD> lds;
+    // the arguments in one go (the compiler would load some of them only where they are used, a scalar
+    // load behind the other)
+    asm volatile("" ::"s"(a.part_o), "s"(a.part_lse), "s"(a.out), "s"(a.out_lse), "s"(a.n_q_heads));
+    if constexpr (PARTS == MergeParts::kExplicit) asm volatile("" ::"s"(a.rows), "s"(a.n_parts));
+    if constexpr (PARTS != MergeParts::kExplicit)
+        asm volatile("" ::"s"(a.slot_rows), "s"(a.group), "s"(a.group_magic), "s"(a.even_bpi), "s"(a.rowrec));
+    if constexpr (STEP)
+        asm volatile("" ::"s"(a.lens), "s"(a.q), "s"(a.k_new), "s"(a.v_new), "s"(a.scale), "s"(a.n_kv_heads),
+                     "s"(a.max_suffix_len), "s"(a.seq_prefix_len), "s"(a.page_table));
+    RowMerge m{};
+    m.part_o = a.part_o;
+    m.part_lse = a.part_lse;
+    int row = blockIdx.x;
+    if constexpr (PARTS == MergeParts::kExplicit) {
+        m.n = a.n_parts;
+        m.p_first = row;
+        m.p_step = a.rows;
+    } else {
+        const int h = blockIdx.x, seq = blockIdx.y;
+        if (STEP && h == a.n_q_heads) {
+            append_token<HD>(a, seq);
+            return;
+        }
+        row = seq * a.n_q_heads + h;
+        const int g = div_magic(h, a.group, a.group_magic);
+        m.p_step = a.slot_rows;
+        if constexpr (PARTS == MergeParts::kEven) {  // item g's blocks g bpi .. write slots vb + g
+            m.n = a.even_bpi;
+            m.p_first = (uint32_t)(g * a.even_bpi + g) * a.slot_rows + seq * a.group + (h - g * a.group);
+        } else if (a.static_split) {
+            // item g owns workers [floor(g NV / Hkv), floor((g+1) NV / Hkv)); its blocks write
+            // their partials to slots vb + g; the one unit starts at sequence 0
+            const int ws0 = static_start(g, a.n_workers, a.n_kv_heads);
+            const int ws1 = static_start(g + 1, a.n_workers, a.n_kv_heads);
+            const int vb0 = ws0 / a.waves;
+            m.n = ws1 > ws0 ? (ws1 - 1) / a.waves - vb0 + 1 : 0;
+            m.p_first = (uint32_t)(vb0 + g) * a.slot_rows + seq * a.group + (h - g * a.group);
+        } else {
+            const int2 rec = *reinterpret_cast<const int2 *>(a.rowrec + (size_t)row * kRowRec);
+            // a record that points outside the workspace (it cannot, unless the workspace was
+            // overwritten from outside) is dropped and flagged rather than followed
+            const int64_t lim = (int64_t)a.n_slots * a.slot_rows;
+            const bool ok = rec.y >= 0 && rec.x >= 0 && (int64_t)rec.x + (int64_t)max(rec.y - 1, 0) * a.slot_rows < lim;
+            if (!ok && threadIdx.x == 0) atomicOr(a.err, kErrBadSchedule);
+            m.p_first = rec.x;
+            m.n = ok ? rec.y : 0;
+        }
+        if constexpr (STEP) {
+            m.len = a.lens + seq;
+            m.max_len = a.max_suffix_len;
+            m.q_row = a.q + (size_t)row * HD;
+            m.k_row = a.k_new + ((size_t)seq * a.n_kv_heads + g) * HD;
+            m.v_row = a.v_new + ((size_t)seq * a.n_kv_heads + g) * HD;
+            m.scale = a.scale;
+        }
+    }
+    m.out_row = a.out + (size_t)row * HD;
+    m.out_lse = a.out_lse ? a.out_lse + row : nullptr;
+    merge_row<HD, STEP>(m, lds);
 }
 
 // The explicit-mode merge for many rows of few parts (the tiled prefill's): HD / 4 lanes per row, each
@@ -317,25 +342,35 @@ bool several_rows_per_block(const MergeArgs &a)
     return !a.plan && (a.n_parts <= kMergeBatch || (a.n_parts <= 4 * kMergeBatch && a.rows >= 2048));
 }
 
+template <int HD>
+void launch_merge_hd(const MergeArgs &a, hipStream_t s)
+{
+    const dim3 block(256);
+    if (several_rows_per_block(a)) {
+        const int per_block = 1024 / HD;
+        merge_rows_kernel<HD><<<dim3((a.rows + per_block - 1) / per_block), block, 0, s>>>(a);
+    } else if (!a.plan) {
+        merge_kernel<HD, MergeParts::kExplicit, false><<<dim3(a.rows), block, 0, s>>>(a);
+    } else {
+        const dim3 rows(a.n_q_heads, a.rows / a.n_q_heads), step(rows.x + 1, rows.y);
+        if (a.even_bpi > 0 && a.step_mode)
+            merge_kernel<HD, MergeParts::kEven, true><<<step, block, 0, s>>>(a);
+        else if (a.even_bpi > 0)
+            merge_kernel<HD, MergeParts::kEven, false><<<rows, block, 0, s>>>(a);
+        else if (a.step_mode)
+            merge_kernel<HD, MergeParts::kPlan, true><<<step, block, 0, s>>>(a);
+        else
+            merge_kernel<HD, MergeParts::kPlan, false><<<rows, block, 0, s>>>(a);
+    }
+}
+
 hipError_t launch_merge(const MergeArgs &a, int head_dim, hipStream_t s)
 {
     if (a.rows <= 0) return hipSuccess;
-    const dim3 grid = a.plan ? dim3(a.n_q_heads, a.rows / a.n_q_heads) : dim3(a.rows), block(256);
-    if (several_rows_per_block(a)) {
-        const int per_block = 1024 / head_dim;
-        const dim3 g((a.rows + per_block - 1) / per_block);
-        if (head_dim == 128)
-            merge_rows_kernel<128><<<g, block, 0, s>>>(a);
-        else if (head_dim == 64)
-            merge_rows_kernel<64><<<g, block, 0, s>>>(a);
-        else
-            return hipErrorInvalidValue;
-        return hipGetLastError();
-    }
     if (head_dim == 128)
-        merge_kernel<128><<<grid, block, 0, s>>>(a);
+        launch_merge_hd<128>(a, s);
     else if (head_dim == 64)
-        merge_kernel<64><<<grid, block, 0, s>>>(a);
+        launch_merge_hd<64>(a, s);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

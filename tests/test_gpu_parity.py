@@ -424,6 +424,37 @@ def test_lse_merge_rows_per_block(fa, d, R, P):
     np.testing.assert_allclose(got[fin], ref_lse[fin], rtol=1e-6, atol=1e-5)
 
 
+@pytest.mark.parametrize("d,P", [(128, 9), (128, 32), (128, 33), (128, 64), (128, 257), (128, 513), (64, 16), (64, 17), (64, 64),
+                                 (64, 65), (64, 256), (64, 300)])
+def test_lse_merge_many_parts(fa, d, P):
+    """The merge of one row per block at the edges of its batches (1, 4 and 8 parts of 8 or 16 slices at a time,
+    64 and 256 lane-wise lse values), with empty parts whose o is NaN, a row without any key and a row
+    with a NaN part, which becomes NaN."""
+    R = 5 if P > 8 * 4 else 1500
+    rng = np.random.default_rng(P)
+    o = rng.standard_normal((P, R, d)).astype(np.float32)
+    l = rng.uniform(-30, 30, (P, R)).astype(np.float32)
+    l[rng.random((P, R)) < 0.3] = -np.inf
+    l[:, 2] = -np.inf
+    l[P // 2, 3] = np.nan
+    l[P - 1, 0] = 40.0  # the last part weighs the most
+    empty = np.isneginf(l)
+    out = torch.full((R, d), 7.0, device="cuda")
+    lse = torch.full((R,), 7.0, device="cuda")
+    fa.lse_merge(torch.from_numpy(np.where(empty[..., None], np.float32("nan"), o)).cuda(), torch.from_numpy(l).cuda(), out, lse)
+    torch.cuda.synchronize()
+    ok = np.arange(R) != 3
+    ref, ref_lse = oracle.lse_merge(np.where(empty[..., None], 0, o).transpose(1, 0, 2).astype(np.float64)[ok], l.T.astype(np.float64)[ok])
+    got_o, got = out.cpu().numpy(), lse.cpu().numpy()
+    assert np.isnan(got_o[3]).all() and np.isnan(got[3])
+    # weights that sum to 1, each of a few ulp (hardware exp2 and reciprocal), and fp32 sums in chains of at
+    # most P / 8 terms: under 1e-5 of |o| <= 5
+    np.testing.assert_allclose(got_o[ok], ref, rtol=1e-5, atol=1e-5)
+    fin = np.isfinite(ref_lse)
+    assert np.array_equal(np.isneginf(got[ok]), ~fin) and np.isneginf(got[2])
+    np.testing.assert_allclose(got[ok][fin], ref_lse[fin], rtol=1e-6, atol=1e-5)
+
+
 def _small_paged(headroom=0, seed=90):
     return W.make(W.CONFIGS["paged"].replace(n_tasks=5, prefix_range=(1, 3000), suffix_range=(0, 400),
                                              page_headroom=headroom, seed=seed))
