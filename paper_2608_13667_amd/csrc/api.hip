@@ -27,6 +27,7 @@ struct fka_plan {
     // eight units, key ranges, whole prefix tiles of 64 keys
     bool prefill_tiles = false;
     int32_t tile_units = 0, tile_unit_groups = 0, tile_ranges = 0, tile_prefix = 0;
+    fka::TileSplit tile_split{};
     int32_t max_suffix_len = 0;
     // contiguous
     int32_t prefix_len = 0, suffix_cap = 0;
@@ -436,6 +437,7 @@ fka_status run_prefill(const fka_plan *p, const fka::AttnArgs &a, float *out, fl
         t.unit_groups = p->tile_unit_groups;
         t.ranges = p->tile_ranges;
         t.prefix_tiles = p->tile_prefix;
+        t.split = p->tile_split;
         t.scale_log2 = p->scale * 1.4426950408889634f;
         e = fka::launch_prefill_tiles(t, p->n_blocks, p->d, s);
         if (e != hipSuccess) return hip_fail(e, "prefill kernel launch");
@@ -496,23 +498,26 @@ struct PrefillLayout {
 };
 
 // Whether an instruction prefill of `rows` query rows per KV head over `keys` prefix keys (summed over
-// the KV heads) takes the tiled kernel or the partial kernel's prefill instantiation.  A tiled call
-// has the longer fixed part (a block's start, two phases per tile, a partial per range: about 25 us
-// from five units on, 19 below, against 15), the instantiation the longer one per unit and key (it
-// loads every key again for each unit of 32 rows).  Measured, us tiled / instantiation, 8 KV heads:
-//   d 128, 8 units: 2000 keys 28.7 / 22.9, 5000 32.4 / 31.9, 14000 40 / 56, 32768 63 / 121
-//          4 units: 2000 20.0 / 17.9, 5000 24.4 / 22.1, 14000 29.1 / 30.7, 32768 44.5 / 57.8
-//          1 unit: 600 15.3 / 17.0, 5000 18.0 / 18.4, 14000 23.6 / 21.3, 32768 37.7 / 34.5
-//   d 64,  8 units: 2000 21.4 / 21.2, 32768 43 / 67; 2 units: 600 13.4 / 18.6, 14000 21.2 / 21.5,
-//          32768 29.3 / 26.2; 1 unit: 2000 14.3 / 13.9, 14000 19.3 / 16.5
-// (2 and 4 KV heads cross at the same products).  From eight units on the tiled kernel throughout.
-bool use_prefill_tiles(int head_dim, int64_t rows, int64_t keys)
+// the KV heads) takes the tiled kernel or the partial kernel's prefill instantiation.  The tiled kernel
+// takes 1.5-2 us for each of a block's steps of 64 keys, however few, and cuts the prefix into at most
+// 256 blocks; the instantiation spreads the smallest call over the whole device, but starts later (16 us
+// against 11) and loads every key again for each unit of 32 rows.  So the tiled kernel is ahead where
+// two steps are enough and where the products count, and behind in between, at d 128.  Measured, us
+// tiled / instantiation, 8 KV heads:
+//   d 128, 1 unit:  600 keys 10.6 / 15.9, 8000 17.0 / 18.0, 14000 20.9 / 20.9, 32768 36.2 / 34.5
+//          3 units: 600 12.5 / 16.3, 3500 17.6 / 17.9, 8000 20.9 / 21.6, 14000 25.4 / 27.6
+//          8 units: 300 19.7 / 19.3, 2000 25.6 / 22.3, 3500 27.9 / 27.0, 5000 27.7 / 31.5, 32768 61 / 120
+//   (2 and 4 KV heads cross at about the same products units x keys; 19 units of 8 KV heads 600 keys
+//   22.7 / 24.7, where the instantiation has no block left for a second range)
+//   d 64,  1 unit:  600 9.3 / 12.7, 14000 16.0 / 15.6, 32768 24.0 / 20.0; 2 units: 14000 17.6 / 19.8, 32768 26.0 / 24.5;
+//          8 units: 2000 19.3 / 19.7, 32768 41 / 66
+bool use_prefill_tiles(int head_dim, int64_t rows, int64_t keys, int64_t n_kv_heads)
 {
-    const int64_t units = (rows + fka::prefill_tiles_unit_rows() - 1) / fka::prefill_tiles_unit_rows();
-    if (rows >= (int64_t)fka::prefill_tiles_waves() * fka::prefill_tiles_unit_rows()) return true;
-    if (head_dim == 64) return units >= 3 || keys <= 40000 * units;
-    if (units == 1) return keys <= 40000;
-    return units >= 3 && units * keys >= (units <= 4 ? 140000 : 300000);
+    const int64_t units = ceil_div(rows, (int64_t)fka::prefill_tiles_unit_rows()), work = units * keys;
+    if (units == 1) return keys <= 100000;
+    if (units == 2) return head_dim == 128 || keys <= 200000;
+    if (head_dim == 64 || units >= 28 || (units >= 8 && units * n_kv_heads >= 128)) return true;
+    return units <= 4 ? work <= 60000 || work >= 190000 : work <= 45000 || work >= 260000;
 }
 
 fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t Lp, int32_t max_suffix_len,
@@ -556,7 +561,7 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device)) != hipSuccess)
         return bail(hip_fail(e, "hipDeviceGetAttribute"));
     const int tile_rows = fka::prefill_tiles_unit_rows(), tile_waves = fka::prefill_tiles_waves();
-    if (use_prefill_tiles(p->d, S * G, (int64_t)Lp * p->Hkv)) {
+    if (use_prefill_tiles(p->d, S * G, (int64_t)Lp * p->Hkv, p->Hkv)) {
         // The tiled kernel: units of 32 consecutive rows of a KV head, eight per block (one per
         // wave) over one of R ranges of the keys, R such that the blocks fill the device.
         const int per_cu = fka::prefill_tiles_blocks_per_cu(p->d, lay.paged);
@@ -568,10 +573,15 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
         const int64_t base = (int64_t)p->Hkv * UG;
         const int64_t want = blocks > 0 ? blocks : (int64_t)cus * per_cu;
         int64_t R = std::max<int64_t>(1, want / base);
-        // at least three tiles to a range: a range costs each row a partial (written, and read by the
-        // merge) and each block a start (measured with 128 tiles, 2 KV heads: 240 rows 26.3 us in 43
-        // ranges, 27.0 in 64, 29.4 in 128, 27.4 in 32; 80 rows 17.3, 17.7, 19.4 and 20.2)
-        R = std::min<int64_t>(R, std::max(1, PT / 3));
+        // A block takes a step per tile of its range and one for a share of the tail keys, which go to the
+        // ranges that have a tile less: fewest steps, two, with two ranges to three tiles, three with
+        // two to five.  A range costs each row a partial (written, and read by the merge), so two steps
+        // pay up to some 28000 floats per row of a unit.  Measured (us; ranges of 1.5 / 2.5 / 3 tiles): d 128, 8 KV heads,
+        // 50 rows 9 tiles 12.8 / 13.6 / 15.8, 31 tiles 14.4 / 15.1 / 16.9, 300 rows 9 tiles 19.6 / 20.2 / 21.7;
+        // 2 KV heads, 320 rows 9 tiles 16.0 / 18.0 / 20.1; on the other side of the line 320 rows 78 tiles
+        // 25.9 / 23.4 / 23.3, 240 rows 128 tiles 28.5 / 27.1 / 27.9.  A tile to a range is no faster (two steps again).
+        const int64_t two = (2 * PT + 2) / 3, three = (2 * PT + 4) / 5;
+        R = std::min<int64_t>(R, std::max<int64_t>(1, two * U * p->d <= 28000 ? two : three));
         // the partials of one range: S Hq rows of d floats; the ranges together stay below 256 MiB
         const int64_t range_bytes = S * p->Hq * (int64_t)p->d * 4;
         R = std::max<int64_t>(1, std::min<int64_t>(R, ((int64_t)256 << 20) / range_bytes));
@@ -580,6 +590,8 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
         p->tile_unit_groups = UG;
         p->tile_ranges = (int32_t)R;
         p->tile_prefix = PT;
+        p->tile_split = fka::TileSplit{fka::exact_div(p->Hkv), fka::exact_div(UG), fka::exact_div(R), fka::exact_div(G),
+                                       fka::exact_div((int64_t)n * G), U / UG, U % UG, PT / (int32_t)R, PT % (int32_t)R};
         for (int32_t u = 0; u < U; ++u) {
             fka::UnitRec r{};
             r.seq0 = (int32_t)(((int64_t)u * tile_rows) / G);

@@ -139,6 +139,27 @@ __host__ __device__ inline int32_t even_split(int32_t j, int32_t q, int32_t r, u
     return j * q + (int32_t)(((uint64_t)(uint32_t)(j * r) * w_magic) >> 32);
 }
 
+// floor(x / d) for any 0 <= x < 2^31 and d >= 1 as a product and a shift: with l = ceil(log2 d) and
+// m = ceil(2^(31+l) / d), m d - 2^(31+l) < d <= 2^l, so that x m / 2^(31+l) is past x / d by less than 1 / d.
+struct ExactDiv {
+    uint32_t m, s;
+};
+__host__ inline ExactDiv exact_div(int64_t d)
+{
+    uint32_t l = 0;
+    while (((int64_t)1 << l) < d) ++l;
+    const unsigned __int128 one = 1;
+    return ExactDiv{(uint32_t)(((one << (31 + l)) + (unsigned __int128)d - 1) / (unsigned __int128)d), 31 + l};
+}
+__host__ __device__ inline int32_t operator/(int32_t x, ExactDiv d) { return (int32_t)(((uint64_t)(uint32_t)x * d.m) >> d.s); }
+
+// The tiled prefill's divisors, and what its split divides for good (fixed by the plan).
+struct TileSplit {
+    ExactDiv kv_heads, unit_groups, ranges, group, branch_rows;  // branch_rows: tokens x G
+    int32_t units_each, units_more;  // units / unit groups, remainder
+    int32_t pre_each, pre_more;      // prefix tiles / ranges, remainder
+};
+
 struct AttnArgs {
     const UnitRec *units;  // [n_units]
     int32_t n_units;
@@ -291,6 +312,7 @@ struct PrefillArgs {
     int32_t ranges;        // R
     int32_t prefix_tiles;  // floor(Lp / 64): whole 64-key tiles
     float scale_log2;      // softmax scale * log2(e)
+    TileSplit split;
 };
 
 // error-flag bits (device)

@@ -253,6 +253,19 @@ __device__ inline bf16x8 join_tr16(vtr_t lo, vtr_t hi)
     return __builtin_bit_cast(bf16x8, v);
 }
 
+// Inclusive sum over the lanes up to this one, in vector-ALU steps (DPP: row_shr, then the sums of the rows
+// below by row_bcast 15 and 31).
+__device__ inline int scan64(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
 // Splits p into hi + lo, both bf16 and both rounded to nearest: what is lost is 2^-18 of p.  (Cutting p off for
 // hi takes as many instructions and loses twice that: 4.5e-6 of a result instead of 2.3e-6.)
 // Packs the values of two key groups (four each) into the B operand of one p.v product.
@@ -342,12 +355,14 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
     // block -> (KV head, unit group, range); the KV head varies fastest so that with Hkv a
     // multiple of 8 a head's blocks all land on one XCD (block b runs on XCD b mod 8)
     const int vb = blockIdx.x;
-    const int g = vb % Hkv, rest = vb / Hkv;
-    const int ug = rest % a.unit_groups, r = rest / a.unit_groups;
+    const int rest = vb / a.split.kv_heads, g = vb - rest * Hkv;
+    const int r = rest / a.split.unit_groups, ug = rest - r * a.unit_groups;
     // the units spread evenly over the groups (at most eight each): blocks of one range then
     // stream its tiles at the same pace, so each tile is fetched once into the XCD's L2 for all
-    const int u = mul_div(ug, a.n_units, a.unit_groups) + wave;
-    const bool active = u < mul_div(ug + 1, a.n_units, a.unit_groups);
+    const int unit_a = ug * a.split.units_each + min(ug, a.split.units_more);
+    const int unit_z = unit_a + a.split.units_each + (ug < a.split.units_more ? 1 : 0);
+    const int u = unit_a + wave;
+    const bool active = u < unit_z;
     const int R = a.ranges;
     const int PT = a.prefix_tiles;
 
@@ -357,8 +372,26 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
     // The ranges share both: range r takes the prefix's tiles [s0, s0 + nmain) (known from the plan, so
     // their loads do not wait for the suffix lengths) and tail tiles [tail_t0, + its share), the
     // first spare tail tile going to the first range without a spare prefix tile.
-    const int pre_each = PT / R, pre_more = PT - pre_each * R;
+    const int pre_each = a.split.pre_each, pre_more = a.split.pre_more;
     const int s0 = r * pre_each + min(r, pre_more), nmain = pre_each + (r < pre_more ? 1 : 0);
+
+    const int row_z = min(rows_head, unit_z * 32);
+    const int br_a = (unit_a * 32) / a.split.branch_rows;
+    const int seq_z = (row_z - 1) / a.split.group, br_z = (row_z - 1) / a.split.branch_rows;
+    const int tail0 = PT * KT, pre_groups = (Lp - tail0 + GRP - 1) / GRP;
+    // Lane i of a chunk of 64 branches: branch br_first + i's length before the instruction, and the
+    // inclusive scan of the branches' groups (br_base groups precede the chunk)
+    int br_len = 0, br_scan = 0, br_first = br_a, br_base = pre_groups, n_groups = 0;
+    auto request_branches = [&](int first) INLINE { return first + lane <= br_z ? a.suffix_len[first + lane] : 0; };
+    auto take_branches = [&](int first, int raw) INLINE {
+        const int b = first + lane;
+        br_len = min(max(raw, 0), a.max_suffix_len - n);
+        if (b <= br_z && br_len != raw) atomicOr(a.err, kErrSuffixClamped);
+        br_scan = scan64(b <= br_z ? (br_len + min(n - 1, seq_z - b * n) + GRP) / GRP : 0);  // (keys + 7) / 8, keys = len + t + 1
+        br_first = first;
+    };
+    // (requested in front of the first tile: loads return in order)
+    const int raw_a = request_branches(br_a);
 
     // DMA: this wave moves tile rows [8 wave, 8 wave + 8): instruction ii writes rows
     // 8 wave + RPI ii + lane / CPR, lane's LDS chunk position lane % CPR, which holds the row's
@@ -419,29 +452,6 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
     // the first tiles' loads go ahead of everything that they do not need
     if (nmain > 0) issue_prefix(s0, 0);
 
-    const int row_a = mul_div(ug, a.n_units, a.unit_groups) * 32;
-    const int row_z = min(rows_head, mul_div(ug + 1, a.n_units, a.unit_groups) * 32);
-    const int br_a = row_a / G / n, seq_z = (row_z - 1) / G, br_z = seq_z / n;
-    const int tail0 = PT * KT, pre_groups = (Lp - tail0 + GRP - 1) / GRP;
-    // Lane i of a chunk of 64 branches: branch br_first + i's length before the instruction, and the
-    // inclusive scan of the branches' groups (br_base groups precede the chunk)
-    int br_len = 0, br_scan = 0, br_first = br_a, br_base = pre_groups, n_groups = 0;
-    auto request_branches = [&](int first) INLINE { return first + lane <= br_z ? a.suffix_len[first + lane] : 0; };
-    auto take_branches = [&](int first, int raw) INLINE {
-        const int b = first + lane;
-        br_len = min(max(raw, 0), a.max_suffix_len - n);
-        if (b <= br_z && br_len != raw) atomicOr(a.err, kErrSuffixClamped);
-        int x = b <= br_z ? (br_len + min(n - 1, seq_z - b * n) + GRP) / GRP : 0;  // (keys + 7) / 8, keys = len + t + 1
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int y = __shfl_up(x, off);
-            if (lane >= off) x += y;
-        }
-        br_scan = x;
-        br_first = first;
-    };
-    const int raw_a = request_branches(br_a);
-
     // ---- query rows (B operand of S^T): lane holds unit row 16 t + l16, d = 32 c + 8 q4 .. +7
     bf16x8 qb[2][NC];
 #pragma unroll
@@ -450,7 +460,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
 #pragma unroll
         for (int c = 0; c < NC; ++c) qb[t][c] = bf16x8{};
         if (active && lr < rows_head) {
-            const int s = lr / G, h = g * G + lr % G;
+            const int s = lr / a.split.group, h = g * G + lr - s * G;
             const uint16_t *qp = a.q + ((size_t)s * Hq + h) * HD + 8 * q4;
 #pragma unroll
             for (int c = 0; c < NC; ++c) qb[t][c] = *reinterpret_cast<const bf16x8 *>(qp + 32 * c);
@@ -530,7 +540,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         }
         take_branches(br_a, request_branches(br_a));
     }
-    const int tail_tiles = (n_groups + NW - 1) / NW, tail_each = tail_tiles / R, tail_more = tail_tiles - tail_each * R;
+    const int tail_tiles = (n_groups + NW - 1) / NW, tail_each = tail_tiles / a.split.ranges, tail_more = tail_tiles - tail_each * R;
     const int tail_pos = r >= pre_more ? r - pre_more : r - pre_more + R;
     const int tail_t0 = tail_pos * tail_each + min(tail_pos, tail_more);
     const int ntot = nmain + tail_each + (tail_pos < tail_more ? 1 : 0);
@@ -666,8 +676,8 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
 #pragma unroll
             for (int t = 0; t < 2; ++t) sc[t][mi] = mfma16(k[c], qb[t][c], sc[t][mi]);
     };
-    // p.v of the tile at buffer offset SOP (PV) and q.k of the one at SO + dyn.
-    auto matrix = [&](auto PVc, auto SOc, auto SOPc, uint32_t dyn, f32x4 (&sc)[2][MT], const bf16x8 (&ph)[2][KS],
+    // p.v of the tile at buffer offset SOP + dynp (PV) and q.k of the one at SO + dyn.
+    auto matrix = [&](auto PVc, auto SOc, auto SOPc, uint32_t dyn, uint32_t dynp, f32x4 (&sc)[2][MT], const bf16x8 (&ph)[2][KS],
                       const bf16x8 (&pl)[2][KS]) INLINE {
         constexpr int first = decltype(PVc)::value ? 0 : NG, last = NG + MT;  // groups: V 0..NG-1, K NG..NG+MT-1
         constexpr int SETS = plan::AHEAD + 1;
@@ -676,7 +686,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         auto request = [&](auto Jc) INLINE {
             constexpr int j = decltype(Jc)::value;
             if constexpr (j < NG)
-                read_v(SOPc, Jc, 0u, v[j % SETS]);
+                read_v(SOPc, Jc, dynp, v[j % SETS]);
             else
                 read_k(SOc, std::integral_constant<int, j - NG>{}, dyn, k[(j - NG) % SETS]);
         };
@@ -727,7 +737,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         using sop_t = std::integral_constant<int, ((B + STAGES - 1) % STAGES) * KBYTES>;
         auto mat = [&]() INLINE {
             __builtin_amdgcn_s_setprio(1);
-            matrix(std::true_type{}, so_t{}, sop_t{}, 0u, sc, ph, pl);
+            matrix(std::true_type{}, so_t{}, sop_t{}, 0u, 0u, sc, ph, pl);
             __builtin_amdgcn_s_setprio(0);
         };
         // the load of tile i + 2, among the softmax's vector work: in front of a matrix phase its scalar
@@ -765,7 +775,8 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         const int lr = u * 32 + 16 * t + l16;
-        row_bt[t] = lr < rows_head ? ((lr / G) / n) << 16 | ((lr / G) % n) : 0x7fff0000;
+        const int br = lr / a.split.branch_rows;
+        row_bt[t] = lr < rows_head ? br << 16 | (lr / a.split.group - br * n) : 0x7fff0000;
     }
     const uint32_t grp0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)&s_grp[0][0] + 8 * (q4 >> 1);
     auto any_qk = [&](int i) INLINE {
@@ -795,7 +806,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
             }
             use = __builtin_amdgcn_ballot_w64(most >= 0) != 0;
         }
-        if (use) matrix(std::false_type{}, zero{}, zero{}, (uint32_t)(i % STAGES) * KBYTES, sc, ph, pl);
+        if (use) matrix(std::false_type{}, zero{}, zero{}, (uint32_t)(i % STAGES) * KBYTES, 0u, sc, ph, pl);
     };
     auto any_sm = [&]() INLINE {
         if (!use) return;
@@ -894,6 +905,37 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
                 any_sm();
         }
     };
+    // Step i between two whole tiles, with the buffers' offsets known at run time: what the unrolled
+    // steps leave over, and ranges too short for them.
+    auto whole_step = [&](int i, auto LEADc) INLINE {
+        constexpr bool LEAD = decltype(LEADc)::value;
+        auto mat = [&]() INLINE {
+            __builtin_amdgcn_s_setprio(1);
+            matrix(std::true_type{}, zero{}, zero{}, (uint32_t)(i % STAGES) * KBYTES, (uint32_t)((i + STAGES - 1) % STAGES) * KBYTES, sc,
+                   ph, pl);
+            __builtin_amdgcn_s_setprio(0);
+        };
+        auto nothing = [&]() INLINE {};
+        if (i + 1 < ntot)
+            wait_vm<2 * DMAS>();
+        else
+            wait_vm<0>();
+        lds_barrier();
+        if (i + 2 < ntot) issue(i + 2);
+        if (active) {
+            if constexpr (LEAD)
+                mat();
+            else
+                sm(sc, ph, pl, nothing);
+        }
+        lds_barrier();
+        if (active) {
+            if constexpr (LEAD)
+                sm(sc, ph, pl, nothing);
+            else
+                mat();
+        }
+    };
     auto run = [&](auto LEADc) INLINE {
         any_step(0, LEADc);
         int i = 1;
@@ -904,6 +946,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
             step(i + 2, std::integral_constant<int, 3>{}, LEADc);
             step(i + 3, std::integral_constant<int, 0>{}, LEADc);
         }
+        for (; i < nmain; ++i) whole_step(i, LEADc);
         for (; i <= ntot; ++i) any_step(i, LEADc);
     };
     if (ntot > 0) {
@@ -927,7 +970,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         const float l = sum_over_rows(l_run[t]);
         const int lr = u * 32 + 16 * t + l16c;
         if (lr >= rows_head) continue;
-        const int s = lr / G, h = g * G + lr % G;
+        const int s = lr / a.split.group, h = g * G + lr - s * G;
         const size_t orow = (size_t)r * rows_total + (size_t)s * Hq + h;
         // a row with no keys in this range: o = 0, lse = -inf (weight 0 in the merge)
         const bool empty = !(l > 0.f) && !(l != l);

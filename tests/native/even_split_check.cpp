@@ -1,7 +1,7 @@
 // Host-side check of the reciprocal forms that a static split of whole blocks uses in place of the
 // general split's divisions (internal.h): div_magic against x / d, and even_split against pre_split and
 // suf_split for every worker, over random sizes up to the bounds they are used within (W <= 1024,
-// slices x W < 2^31) and the small ones exhaustively.  Prints "ok <cases>" or the first failure.
+// slices x W < 2^31) and the small ones exhaustively; ExactDiv over all dividends and divisors.  Prints "ok <cases>" or the first failure.
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -46,6 +46,14 @@ int main(int argc, char **argv)
             const uint32_t x = (uint32_t)(rng() % last) & 0x7fffffffu;
             if (div_magic((int32_t)x, (int32_t)d, m) != (int32_t)(x / d)) return std::printf("FAIL %u / %u\n", x, d), 1;
         }
+    }
+    for (int c = 0; c < 200000 + cases; ++c, ++n) {  // ExactDiv: any divisor, any 31-bit dividend
+        const int64_t d = c < 4096 ? c + 1 : 1 + (int64_t)(rng() % ((uint64_t)1 << (1 + rng() % 31)));
+        const ExactDiv e = exact_div(d);
+        const int64_t top = 0x7fffffff, q = (int64_t)(rng() % (uint64_t)(top / d + 1)) * d;
+        for (int64_t x : {(int64_t)0, d - 1, d, q - 1, q, q + d - 1, top / d * d - 1, top / d * d, top, (int64_t)(rng() & 0x7fffffff)})
+            if (x >= 0 && x <= top && (int32_t)x / e != (int32_t)(x / d))
+                return std::printf("FAIL %lld / %lld\n", (long long)x, (long long)d), 1;
     }
     std::printf("ok %ld\n", n);
     return 0;

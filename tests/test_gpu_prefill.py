@@ -252,14 +252,26 @@ def test_prefill_tiled_moving_reference(fa, how):
 
 @pytest.mark.parametrize("c,tiled", [
     (dict(head_dim=128, n_kv_heads=2, n_q_heads=2, n_branches=4, n=8, prefix_len=1100), True),     # 1 unit, few keys
-    (dict(head_dim=128, n_kv_heads=8, n_q_heads=8, n_branches=3, n=11, prefix_len=700), False),    # 2 units
-    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=2950), True),  # 3 units, 47200 keys
-    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=2900), False),
-    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4700), True),  # 8 units, 254 rows
-    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4600), False),
-    (dict(head_dim=64, n_kv_heads=8, n_q_heads=8, n_branches=2, n=16, prefix_len=4999), True),     # 1 unit, 39992 keys
-    (dict(head_dim=64, n_kv_heads=8, n_q_heads=8, n_branches=2, n=16, prefix_len=5001), False),
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=6250), True),   # 100000 keys
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=6251), False),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=8, n_branches=3, n=11, prefix_len=700), True),     # 2 units
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=1250), True),  # 3 units, 20000 keys
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=1251), False),
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=3958), False),
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=3959), True),  # 63344 keys
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=703), True),   # 8 units, 254 rows
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=704), False),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4062), False),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4063), True),
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=32, n_branches=1, n=127, prefix_len=900), True),  # 128 units in all
+    (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=4, n=43, prefix_len=3000), False),  # 27 units
+    (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=4, n=44, prefix_len=3000), True),   # 28 units
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=16, prefix_len=6250), True),   # 1 unit, 100000 keys
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=16, prefix_len=6251), False),
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=17, prefix_len=12500), True),  # 2 units, 200000 keys
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=17, prefix_len=12501), False),
     (dict(head_dim=64, n_kv_heads=2, n_q_heads=10, n_branches=3, n=5, prefix_len=63), True),       # 3 units, no whole tile
+    (dict(head_dim=64, n_kv_heads=2, n_q_heads=10, n_branches=3, n=5, prefix_len=64), True),       # one tile
     (dict(head_dim=64, n_kv_heads=4, n_q_heads=28, n_branches=2, n=37, prefix_len=833), True),     # 17 units
 ], ids=lambda x: x if isinstance(x, bool) else f"d{x['head_dim']}-kv{x['n_kv_heads']}-n{x['n']}-p{x['prefix_len']}")
 def test_prefill_kernel_choice(fa, c, tiled):
