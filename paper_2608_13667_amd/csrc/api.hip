@@ -23,6 +23,8 @@ struct fka_plan {
     int32_t prefill_n = 0;     // instruction prefill plan: tokens per branch (sequences are b * n + t)
     int32_t n_branches = 0;    // instruction prefill plan: branches
     int32_t prefill_groups = 1; // instruction prefill plan: units per block
+    int32_t set_blocks = 1;     // ... blocks per set of units
+    fka::ExactDiv by_prefill_n{}, by_sets{}, by_kv_heads{};
     // instruction prefill on the tiled kernel: 32-row units per KV head, blocks of
     // eight units, key ranges, whole prefix tiles of 64 keys
     bool prefill_tiles = false;
@@ -140,6 +142,7 @@ void init_heads(fka_plan *p, const fka_heads *h)
     p->Hkv = h->n_kv_heads;
     p->d = h->head_dim;
     p->G = p->Hq / p->Hkv;
+    p->by_kv_heads = fka::exact_div(p->Hkv);
     p->scale = h->softmax_scale > 0.f ? h->softmax_scale : 1.0f / std::sqrt((float)h->head_dim);
 }
 
@@ -355,6 +358,10 @@ fka::AttnArgs attn_args(const fka_plan *p)
     a.n_pool_pages = p->n_pool_pages;
     a.paged = p->paged ? 1 : 0;
     a.prefill_groups = p->prefill_groups;
+    a.set_blocks = p->set_blocks;
+    a.by_prefill_n = p->by_prefill_n;
+    a.by_sets = p->by_sets;
+    a.by_kv_heads = p->by_kv_heads;
     return a;
 }
 
@@ -653,6 +660,9 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
     p->row_tiles = best_tiles;
     p->waves = waves;
     p->prefill_groups = P;
+    p->set_blocks = best_B;
+    p->by_prefill_n = fka::exact_div(n);
+    p->by_sets = fka::exact_div(sets);
     p->n_blocks = (int32_t)(best_B * sets);
     p->rounds = 1;
     p->n_slots = best_B * p->n_items;

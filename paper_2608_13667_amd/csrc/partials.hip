@@ -275,6 +275,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
     // per wave: item (-1: none), unit, item workers W, the group's first and end worker within
     // the item, the group's first and end wave within the block
     __shared__ int32_t s_wf[NW][7];
+    // proportional split: per wave, the item whose first worker it is: unit (-1: none), KV head, first slot, slots
+    __shared__ __attribute__((aligned(16))) int32_t s_rec[NW][4];
     __shared__ __attribute__((aligned(16))) int32_t s_grp[NW][4];  // the block's groups: first wave, end wave, rows, item
     __shared__ int32_t s_ngrp;
 
@@ -350,19 +352,30 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             if (lane == 0) s_ngrp = __builtin_popcountll(m);
         }
     } else {
-        // one round trip: the suffix lengths and the units; then the scans and the placement
+        // one round trip: the suffix lengths and the units (both requested before either is waited for);
+        // then the scans and the placement
         bool clamped = false;
+        const int32_t *ur = reinterpret_cast<const int32_t *>(a.units);
+        int raw0 = 0, u0 = 0, u1 = 0, u2 = 0, u3 = 0;
+        if (tid < N) raw0 = a.suffix_len[PREFILL ? tid / a.by_prefill_n : tid];
+        if (tid < a.n_units) {
+            u0 = ur[4 * tid + 0];
+            u1 = ur[4 * tid + 1];
+            u2 = ur[4 * tid + 2];
+            u3 = ur[4 * tid + 3];
+        }
+        asm volatile("" : "+v"(raw0), "+v"(u0), "+v"(u1), "+v"(u2), "+v"(u3));
         for (int s = tid; s < N; s += NTH) {
             int L;
             if constexpr (PREFILL) {
                 // instruction token t of branch b (s = b n + t) sees b's suffix up to its own position
-                const int n = a.prefill_n;
-                const int raw = a.suffix_len[s / n];
+                const int n = a.prefill_n, b = s / a.by_prefill_n;
+                const int raw = s == tid ? raw0 : a.suffix_len[b];
                 const int Lb = min(max(raw, 0), max_len - n);
                 clamped |= (Lb != raw);
-                L = Lb + s % n + 1;
+                L = Lb + s - b * n + 1;
             } else {
-                const int raw = a.suffix_len[s];
+                const int raw = s == tid ? raw0 : a.suffix_len[s];
                 L = min(max(raw, 0), max_len);
                 clamped |= (L != raw);
             }
@@ -370,15 +383,15 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             s_cs[s] = slices_of(L);
             if (vb == 0) a.lens[s] = L;  // what the merge appends at
         }
-        const int32_t *ur = reinterpret_cast<const int32_t *>(a.units);
         for (int u = tid; u < a.n_units; u += NTH) {
-            s_u0[u] = ur[4 * u + 0];
-            s_un[u] = ur[4 * u + 1];
-            s_ul[u] = ur[4 * u + 2];
-            s_up[u] = ur[4 * u + 3];
+            s_u0[u] = u == tid ? u0 : ur[4 * u + 0];
+            s_un[u] = u == tid ? u1 : ur[4 * u + 1];
+            s_ul[u] = u == tid ? u2 : ur[4 * u + 2];
+            s_up[u] = u == tid ? u3 : ur[4 * u + 3];
         }
         if (vb == 0 && clamped) atomicOr(a.err, kErrSuffixClamped);
-        if (tid < NW) s_wf[tid][0] = -1;  // waves the placement below does not reach have no item
+        if (tid < NW) s_wf[tid][0] = -1;   // waves the placement below does not reach have no item
+        if (tid < NW) s_rec[tid][0] = -1;  // and start none
         if constexpr (PREFILL) {
             // Cyclic placement over block sets: a set is P = prefill_groups units of one KV head
             // (its blocks split into P groups of NW / P waves, group j taking the set's j-th unit
@@ -387,10 +400,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             // B = blocks / n_sets blocks.  With n_sets a multiple of the 8 XCDs, every block of a
             // KV head runs on one XCD, so the blocks of one prefix range, one per unit, share its
             // tiles through that XCD's L2.
-            const int P = a.prefill_groups, GW = NW / P;
-            const int n_sets = (a.n_units + P - 1) / P * Hkv, B = (int)gridDim.x / n_sets;
-            const int set = vb % n_sets, k = vb / n_sets;
-            const int g = set % Hkv, us = set / Hkv;
+            const int P = a.prefill_groups, GW = NW >> (P - 1), B = a.set_blocks;
+            const int k = vb / a.by_sets, set = vb - k * (((a.n_units + P - 1) >> (P - 1)) * Hkv);
+            const int us = set / a.by_kv_heads, g = set - us * Hkv;
             lds_barrier();  // the unit table
             if (tid < NW) {
                 const int grp = tid / GW, u = us * P + grp;
@@ -408,7 +420,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
                     const int u = us * P + grp, i = u * Hkv + g;
                     if (u >= a.n_units) break;
                     for (int r = tid; r < s_un[u] * G; r += NTH) {
-                        int32_t *rr = a.rowrec + ((size_t)(s_u0[u] + r / G) * a.n_q_heads + g * G + r % G) * kRowRec;
+                        const int rq = div_magic(r, G, a.group_magic);
+                        int32_t *rr = a.rowrec + ((size_t)(s_u0[u] + rq) * a.n_q_heads + g * G + r - rq * G) * kRowRec;
                         rr[0] = i * B * a.slot_rows + r;
                         rr[1] = B;
                     }
@@ -422,12 +435,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
                 for (int base = 0; base < n; base += NTH) {
                     const int i = base + tid;
                     const int x0 = i < n ? v[i] : 0;
-                    int x = x0;
-#pragma unroll
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const int y = __shfl_up(x, off);
-                        if (lane >= off) x += y;
-                    }
+                    const int x = scan64(x0);
                     if (lane == 63) s_wsum[wave] = x;
                     lds_barrier();
                     int pre = carry;
@@ -452,9 +460,11 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             const uint64_t R = T > 0 ? sched_ratio((int64_t)NV - NNE, T) : 0;
             const int n_items = a.n_units * Hkv;
             // every thread places its items' workers of this block; the block holding an item's
-            // first worker writes the slot records of the item's rows (block 0 those of empty items)
+            // first worker writes the slot records of the item's rows (later, a wave per item: a
+            // thread alone would take some 300 cycles a row, with the block waiting for it), block 0
+            // those of empty items
             for (int i = tid; i < n_items; i += NTH) {
-                const int u = i / Hkv, g = i - u * Hkv;
+                const int u = i / a.by_kv_heads, g = i - u * Hkv;
                 const int u0 = s_u0[u], un = s_un[u];
                 const int size = slices_of(s_ul[u]) + s_cs[u0 + un] - s_cs[u0];
                 const int64_t C = (int64_t)Hkv * (s_up[u] + s_cs[u0]) + (int64_t)g * size;
@@ -464,12 +474,18 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
                     ws0 = worker_start(C, K, R);
                     ws1 = worker_start(C + size, K + 1, R);
                 }
-                if ((ws1 > ws0 && ws0 >= w_lo && ws0 < w_lo + NW) || (ws1 == ws0 && vb == 0)) {
-                    const int first = ws1 > ws0 ? ws0 / NW + i : 0, count = ws1 > ws0 ? (ws1 - 1) / NW - ws0 / NW + 1 : 0;
+                if (ws1 > ws0 && ws0 >= w_lo && ws0 < w_lo + NW) {
+                    int32_t *d = s_rec[ws0 - w_lo];
+                    d[0] = u;
+                    d[1] = g;
+                    d[2] = ws0 / NW + i;
+                    d[3] = (ws1 - 1) / NW - ws0 / NW + 1;
+                } else if (ws1 == ws0 && vb == 0) {
                     for (int r = 0; r < un * G; ++r) {
-                        int32_t *rr = a.rowrec + ((size_t)(u0 + r / G) * a.n_q_heads + g * G + r % G) * kRowRec;
-                        rr[0] = first * a.slot_rows + r;
-                        rr[1] = count;
+                        const int rq = div_magic(r, G, a.group_magic);
+                        int32_t *rr = a.rowrec + ((size_t)(u0 + rq) * a.n_q_heads + g * G + r - rq * G) * kRowRec;
+                        rr[0] = r;
+                        rr[1] = 0;
                     }
                 }
                 if (ws1 <= w_lo || ws0 >= w_lo + NW || ws1 <= ws0) continue;
@@ -514,7 +530,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
         }
     }
 
-    const int kvh = item >= 0 ? item % Hkv : 0;
+    const int kvh = item >= 0 ? item - unit * Hkv : 0;
     const int rows = nseq * G;
     const int nt_act = (rows + 15) >> 4;
     const int Ps = slices_of(plen);
@@ -571,12 +587,12 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             s.kb = arg_kp;
             s.vb = arg_vp;
             // the prefill's virtual sequence reads its branch's page-table row
-            const int prow = PREFILL ? (iss ? seq : seq0) / a.prefill_n : (iss ? seq : seq0);
+            const int prow = PREFILL ? (iss ? seq : seq0) / a.by_prefill_n : (iss ? seq : seq0);
             s.ptab = uni_ptr(arg_pt + (size_t)prow * arg_maxp);
             s.page_off = iss ? (plen + kPageSize - 1) / kPageSize : 0;
         } else {
             const size_t pbase = (size_t)kvh * (size_t)arg_plen * ROWB;
-            const int buf = PREFILL ? seq / a.prefill_n : seq;  // prefill: branch b's buffer
+            const int buf = PREFILL ? seq / a.by_prefill_n : seq;  // prefill: branch b's buffer
             const size_t sbase = ((size_t)buf * Hkv + kvh) * (size_t)arg_cap * ROWB;
             s.kb = iss ? arg_sk + sbase : arg_pk + pbase;
             s.vb = iss ? arg_sv + sbase : arg_pv + pbase;
@@ -679,6 +695,18 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
         load_k(sc, kbuf[0]);
     }
 
+    // ---- proportional split: the slot records of the item that starts at this wave
+    if (!PREFILL && !static_split && s_rec[wave][0] >= 0) {
+        const int4 rec = *reinterpret_cast<const int4 *>(&s_rec[wave][0]);
+        const int rows_u = s_un[rec.x] * G;
+        for (int r = lane; r < rows_u; r += 64) {
+            const int rq = div_magic(r, G, a.group_magic);
+            int32_t *rr = a.rowrec + ((size_t)(s_u0[rec.x] + rq) * a.n_q_heads + rec.y * G + r - rq * G) * kRowRec;
+            rr[0] = rec.z * a.slot_rows + r;
+            rr[1] = rec.w;
+        }
+    }
+
     // ---- the suffix part of the schedule
     if (static_split) {
         const int L = min(max(lraw, 0), max_len);
@@ -690,15 +718,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
     } else if (item >= 0) {
         lenv = lane < nseq ? s_len[seq0 + lane] : 0;
     }
-    {
-        int x = slices_of(lenv);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int y = __shfl_up(x, off);
-            if (lane >= off) x += y;
-        }
-        csv = x;
-    }
+    csv = scan64(slices_of(lenv));
     if (item >= 0) {
         const int S = __builtin_amdgcn_readlane(csv, 63);
         if (even) {
@@ -1010,13 +1030,17 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             asm volatile("" ::"v"(gi.x), "v"(gi.y), "v"(gi.z), "v"(gi.w));  // one LDS read, not four
             const int lw = gi.x, ge = gi.y, it = gi.w;
             // the group's slot: vb + it, or under the cyclic placement it B + (vb / n_sets)
-            const int n_sets_c = (a.n_units + a.prefill_groups - 1) / a.prefill_groups * Hkv;
-            const int slot_c = PREFILL ? it * ((int)gridDim.x / n_sets_c) + vb / n_sets_c : vb + it;
+            const int slot_c = PREFILL ? it * a.set_blocks + vb / a.by_sets : vb + it;
             if (slot_c >= a.n_slots || it < 0) continue;  // never store outside the workspace
             const int r0 = 16 * TPP * pass, r1 = min(gi.z, r0 + 16 * TPP);
             const bool whole = lw == 0 && ge == NW;  // the usual case: one group, all waves
-            for (int u = tid_c; u < (r1 - r0) * CHU; u += NTH)
-                piece(pass, r0 + u % (r1 - r0), u / (r1 - r0), lw, ge, whole, slot_c);
+            // u / n by a reciprocal: u < 64 x 32, so the product is off by less than 1 / (2 n)
+            const int n = r1 - r0;
+            const float inv_n = __builtin_amdgcn_rcpf((float)n);
+            for (int u = tid_c; u < n * CHU; u += NTH) {
+                const int cu = (int)(((float)u + 0.5f) * inv_n);
+                piece(pass, r0 + u - cu * n, cu, lw, ge, whole, slot_c);
+            }
         }
     }
     if (bad_page) atomicOr(a.err, kErrBadPage);

@@ -253,19 +253,6 @@ __device__ inline bf16x8 join_tr16(vtr_t lo, vtr_t hi)
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// Inclusive sum over the lanes up to this one, in vector-ALU steps (DPP: row_shr, then the sums of the rows
-// below by row_bcast 15 and 31).
-__device__ inline int scan64(int x)
-{
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-    return x;
-}
-
 // Splits p into hi + lo, both bf16 and both rounded to nearest: what is lost is 2^-18 of p.  (Cutting p off for
 // hi takes as many instructions and loses twice that: 4.5e-6 of a result instead of 2.3e-6.)
 // Packs the values of two key groups (four each) into the B operand of one p.v product.
