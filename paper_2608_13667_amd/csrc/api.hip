@@ -507,24 +507,26 @@ struct PrefillLayout {
 // Whether an instruction prefill of `rows` query rows per KV head over `keys` prefix keys (summed over
 // the KV heads) takes the tiled kernel or the partial kernel's prefill instantiation.  The tiled kernel
 // takes 1.5-2 us for each of a block's steps of 64 keys, however few, and cuts the prefix into at most
-// 256 blocks; the instantiation spreads the smallest call over the whole device, but starts later (16 us
+// 256 blocks; the instantiation spreads the smallest call over the whole device, but starts later (15 us
 // against 11) and loads every key again for each unit of 32 rows.  So the tiled kernel is ahead where
-// two steps are enough and where the products count, and behind in between, at d 128.  Measured, us
-// tiled / instantiation, 8 KV heads:
-//   d 128, 1 unit:  600 keys 10.6 / 15.9, 8000 17.0 / 18.0, 14000 20.9 / 20.9, 32768 36.2 / 34.5
-//          3 units: 600 12.5 / 16.3, 3500 17.6 / 17.9, 8000 20.9 / 21.6, 14000 25.4 / 27.6
-//          8 units: 300 19.7 / 19.3, 2000 25.6 / 22.3, 3500 27.9 / 27.0, 5000 27.7 / 31.5, 32768 61 / 120
-//   (2 and 4 KV heads cross at about the same products units x keys; 19 units of 8 KV heads 600 keys
-//   22.7 / 24.7, where the instantiation has no block left for a second range)
-//   d 64,  1 unit:  600 9.3 / 12.7, 14000 16.0 / 15.6, 32768 24.0 / 20.0; 2 units: 14000 17.6 / 19.8, 32768 26.0 / 24.5;
-//          8 units: 2000 19.3 / 19.7, 32768 41 / 66
+// two steps are enough and where the products count, and behind in between.  Measured, us tiled /
+// instantiation, 8 KV heads where nothing else is said:
+//   d 128, 1 unit:  600 keys 10.6 / 14.4, 8000 17.0 / 17.2, 14000 21.0 / 20.3, 32768 36.1 / 32.5
+//          3 units: 600 12.5 / 14.9, 3500 17.7 / 16.1, 8000 20.9 / 21.4, 14000 25.6 / 27.3
+//          8 units: 300 18.6 / 18.0, 2000 25.5 / 21.0, 3500 27.9 / 26.0, 5000 27.8 / 30.5, 32768 61 / 120
+//   (2 and 4 KV heads cross at about the same products units x keys; 19 units of 8 KV heads, 600 keys
+//   22.5 / 23.6, 2000 28.5 / 35.9, where the instantiation has no block left for a second range)
+//   d 64,  1 unit:  600 9.2 / 11.7, 8000 13.1 / 13.4, 14000 15.9 / 14.6; 2 units: 14000 17.4 / 18.9, 32768 26.0 / 23.2;
+//          8 units: 2000 19.2 / 19.0, 32768 41 / 65; 2 KV heads 8000 16.9 / 17.4, 14000 19.1 / 18.0, 32768 24.0 / 23.1
 bool use_prefill_tiles(int head_dim, int64_t rows, int64_t keys, int64_t n_kv_heads)
 {
     const int64_t units = ceil_div(rows, (int64_t)fka::prefill_tiles_unit_rows()), work = units * keys;
-    if (units == 1) return keys <= 100000;
-    if (units == 2) return head_dim == 128 || keys <= 200000;
-    if (head_dim == 64 || units >= 28 || (units >= 8 && units * n_kv_heads >= 128)) return true;
-    return units <= 4 ? work <= 60000 || work >= 190000 : work <= 45000 || work >= 260000;
+    if (units == 1) return keys <= 60000;
+    if (units == 2) return head_dim == 128 || keys <= 120000;
+    if (units >= 28 || (units >= 8 && units * n_kv_heads >= 128)) return true;
+    if (head_dim == 64) return units < 7 || units * n_kv_heads > 60 || work <= 130000 || work >= 430000;
+    if (units <= 4) return work <= 60000 || work >= 190000;
+    return work <= (units <= 8 ? 20000 : 45000) || work >= 270000;
 }
 
 fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t Lp, int32_t max_suffix_len,

@@ -233,7 +233,7 @@ def test_prefill_tiled_moving_reference(fa, how):
     the old reference), that fall (p underflows), and a first tile far below or above the rest; a
     prefix of whole tiles and 37 more keys, suffixes of 300-330 keys, whose tail tiles are shared by
     all ranges.  Every row checked, contiguous and paged."""
-    n = 20
+    n = 60
     w = W.make(W.CONFIGS["mid"].replace(n_kv_heads=2, n_q_heads=8, n_branches=4, prefix_len=1509,
                                         suffix_range=(300, 330), steps=n, seed=2765))
     _scored(w, how)
@@ -252,24 +252,28 @@ def test_prefill_tiled_moving_reference(fa, how):
 
 @pytest.mark.parametrize("c,tiled", [
     (dict(head_dim=128, n_kv_heads=2, n_q_heads=2, n_branches=4, n=8, prefix_len=1100), True),     # 1 unit, few keys
-    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=6250), True),   # 100000 keys
-    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=6251), False),
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=3750), True),   # 60000 keys
+    (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=3751), False),
     (dict(head_dim=128, n_kv_heads=8, n_q_heads=8, n_branches=3, n=11, prefix_len=700), True),     # 2 units
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=1250), True),  # 3 units, 20000 keys
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=1251), False),
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=3958), False),
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=3959), True),  # 63344 keys
-    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=703), True),   # 8 units, 254 rows
-    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=704), False),
-    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4062), False),
-    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4063), True),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=312), True),   # 8 units, 254 rows
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=313), False),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4218), False),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=16, n_branches=1, n=127, prefix_len=4219), True),
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=32, n_branches=1, n=127, prefix_len=900), True),  # 128 units in all
     (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=4, n=43, prefix_len=3000), False),  # 27 units
     (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=4, n=44, prefix_len=3000), True),   # 28 units
-    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=16, prefix_len=6250), True),   # 1 unit, 100000 keys
-    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=16, prefix_len=6251), False),
-    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=17, prefix_len=12500), True),  # 2 units, 200000 keys
-    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=17, prefix_len=12501), False),
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=16, prefix_len=3750), True),   # 1 unit, 60000 keys
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=16, prefix_len=3751), False),
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=17, prefix_len=7500), True),   # 2 units, 120000 keys
+    (dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=2, n=17, prefix_len=7501), False),
+    (dict(head_dim=64, n_kv_heads=2, n_q_heads=4, n_branches=1, n=127, prefix_len=8125), True),    # 8 units, 16250 keys
+    (dict(head_dim=64, n_kv_heads=2, n_q_heads=4, n_branches=1, n=127, prefix_len=8126), False),
+    (dict(head_dim=64, n_kv_heads=2, n_q_heads=4, n_branches=1, n=127, prefix_len=26874), False),
+    (dict(head_dim=64, n_kv_heads=2, n_q_heads=4, n_branches=1, n=127, prefix_len=26875), True),
     (dict(head_dim=64, n_kv_heads=2, n_q_heads=10, n_branches=3, n=5, prefix_len=63), True),       # 3 units, no whole tile
     (dict(head_dim=64, n_kv_heads=2, n_q_heads=10, n_branches=3, n=5, prefix_len=64), True),       # one tile
     (dict(head_dim=64, n_kv_heads=4, n_q_heads=28, n_branches=2, n=37, prefix_len=833), True),     # 17 units
