@@ -153,19 +153,6 @@ __host__ inline ExactDiv exact_div(int64_t d)
 }
 __host__ __device__ inline int32_t operator/(int32_t x, ExactDiv d) { return (int32_t)(((uint64_t)(uint32_t)x * d.m) >> d.s); }
 
-// Inclusive sum over the lanes up to this one, in vector-ALU steps (DPP: row_shr, then the sums of the rows
-// below by row_bcast 15 and 31); a scan of six shuffles is as many LDS round trips.
-__device__ inline int scan64(int x)
-{
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-    return x;
-}
-
 // The tiled prefill's divisors, and what its split divides for good (fixed by the plan).
 struct TileSplit {
     ExactDiv kv_heads, unit_groups, ranges, group, branch_rows;  // branch_rows: tokens x G

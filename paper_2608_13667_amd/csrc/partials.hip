@@ -34,6 +34,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "scan64.h"
 
 namespace fka {
 namespace {

@@ -49,6 +49,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "scan64.h"
 
 namespace fka {
 namespace {
