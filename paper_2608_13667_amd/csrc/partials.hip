@@ -314,7 +314,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
         nseq = N;
         plen = a.prefix_len;
         if (even) {
-            // whole blocks per item, in multiplications by the host's reciprocals
+            // whole blocks per item, in multiplications by the host's reciprocals (ten divisions in a row
+            // stood in front of the first loads: with the merge's five 19.7 us a step against 18.2 at 8k keys)
             item = div_magic(vb, a.even.bpi, a.even.bpi_magic);
             const int k = vb - item * a.even.bpi;
             Wi = a.even.bpi * NW;
@@ -462,8 +463,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
             const int n_items = a.n_units * Hkv;
             // every thread places its items' workers of this block; the block holding an item's
             // first worker writes the slot records of the item's rows (later, a wave per item: a
-            // thread alone would take some 300 cycles a row, with the block waiting for it), block 0
-            // those of empty items
+            // thread alone would take some 300 cycles a row, with the block waiting for it: 5 forks of 500
+            // keys 25.0 us against 22.4 with the rest of the set-up), block 0 those of empty items
             for (int i = tid; i < n_items; i += NTH) {
                 const int u = i / a.by_kv_heads, g = i - u * Hkv;
                 const int u0 = s_u0[u], un = s_un[u];

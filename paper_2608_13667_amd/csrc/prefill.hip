@@ -43,8 +43,14 @@
 // (124 steps, 32k prefix, 64 tokens x 5 branches, 40 / 8 heads), where the chip's power limit holds
 // the clock at 2.2 of 2.4 GHz.  With the operands read in bursts that were waited for whole, a
 // maximum per tile and the keys past the whole tiles read wave by wave, one round trip to memory per
-// 32 keys (25000 cycles in the last range), it took 4920: 292 us a call against 268 now, 233
-// against 215 at 256 tokens x 1 sequence over 33.8k keys, 74.5 against 70 at 16 x 5 over 23k.
+// 32 keys (25000 cycles in the last range), it took 4920: 292 us a call against 265 now, 235
+// against 211 at 256 tokens x 1 sequence over 33.8k keys, 74.5 against 65.5 at 16 x 5 over 23k.  (The sums
+// of p as one more d tile of ones take 24 vector slots away and add 8 products: 277 us; the products' energy
+// counts, not the slots.)
+// A call of few keys per block is bound by its start and by whole steps of 1.5-2 us: the split's divisors
+// come from the plan as exact products, the lengths are requested ahead of the tiles, and the
+// ranges are cut for two steps where the partials stay small (1.2 us less of start, 1.7 us per step not
+// taken: 320 rows 600 keys, 2 KV heads, 20.1 us against 14.9; 50 rows 2000 keys, 8 KV heads, 17.0 against 13.1).
 #include <type_traits>
 #include <utility>
 
@@ -894,7 +900,8 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         }
     };
     // Step i between two whole tiles, with the buffers' offsets known at run time: what the unrolled
-    // steps leave over, and ranges too short for them.
+    // steps leave over, and ranges too short for them (the general step instead costs 0.3-0.5 us more each:
+    // 5-7 tiles a block, 29.2 us against 27.8 at 320 rows 32k keys, 1 KV head).
     auto whole_step = [&](int i, auto LEADc) INLINE {
         constexpr bool LEAD = decltype(LEADc)::value;
         auto mat = [&]() INLINE {
