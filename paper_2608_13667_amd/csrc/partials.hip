@@ -450,12 +450,26 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<HD, NT, PAGED, PREFILL>()))) v
                 }
                 if (tid == 0) v[n] = carry;
             };
-            block_scan(s_cs, N);
-            lds_barrier();
-            for (int u = tid; u < a.n_units; u += NTH)
-                s_ne[u] = (slices_of(s_ul[u]) + s_cs[s_u0[u] + s_un[u]] - s_cs[s_u0[u]]) > 0 ? 1 : 0;
-            lds_barrier();
-            block_scan(s_ne, a.n_units);
+            if (N <= 64 && a.n_units <= 64) {  // one wave scans both, at one barrier instead of seven (0.6-0.9 us)
+                if (wave == 0) {
+                    const int c0 = lane < N ? s_cs[lane] : 0, c = scan64(c0);
+                    if (lane < N) s_cs[lane] = c - c0;
+                    if (lane == 63) s_cs[N] = c;
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    const bool u = lane < a.n_units;
+                    const int u0 = u ? s_u0[lane] : 0;
+                    const int e0 = u && slices_of(s_ul[lane]) + s_cs[u0 + s_un[lane]] - s_cs[u0] > 0 ? 1 : 0, e = scan64(e0);
+                    if (u) s_ne[lane] = e - e0;
+                    if (lane == 63) s_ne[a.n_units] = e;
+                }
+            } else {
+                block_scan(s_cs, N);
+                lds_barrier();
+                for (int u = tid; u < a.n_units; u += NTH)
+                    s_ne[u] = (slices_of(s_ul[u]) + s_cs[s_u0[u] + s_un[u]] - s_cs[s_u0[u]]) > 0 ? 1 : 0;
+                lds_barrier();
+                block_scan(s_ne, a.n_units);
+            }
             lds_barrier();
             const int T = __builtin_amdgcn_readfirstlane(Hkv * (a.ps_total + s_cs[N]));  // total slices
             const int NNE = __builtin_amdgcn_readfirstlane(Hkv * s_ne[a.n_units]);      // non-empty items

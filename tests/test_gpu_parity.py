@@ -504,6 +504,22 @@ def test_paged_small_parity_and_naive(fa):
         gates.assert_lse(lse, ref_lse, what=f"paged share={share}")
 
 
+@pytest.mark.parametrize("tasks,branches", [(16, 4), (13, 5)])
+def test_proportional_set_up_at_64_sequences(fa, tasks, branches):
+    """The proportional split's scans by one wave (up to 64 sequences and units) and by the block (more),
+    with as many units as tasks and as sequences, some short enough to have no second worker."""
+    w = W.make(W.CONFIGS["paged"].replace(n_tasks=tasks, n_branches=branches, n_kv_heads=2, n_q_heads=8, prefix_range=(1, 600),
+                                          suffix_range=(0, 60), seed=97))
+    ref, ref_lse = oracle.decode_workload(w)
+    dv = to_dev_paged(w)
+    for share in (True, False):
+        plan = paged_plan(fa, w, share_prefix=share)
+        assert plan.info().static_split == 0 and plan.info().n_units == (tasks if share else tasks * branches)
+        out, lse = run_paged(plan, dv)
+        gates.assert_gates(out, ref, what=f"{tasks} x {branches}, share={share}")
+        gates.assert_lse(lse, ref_lse, what=f"{tasks} x {branches}, share={share}")
+
+
 def test_paged_equals_contiguous_on_same_data(fa):
     """The paged path and the contiguous path agree on one task's gathered data."""
     w = _small_paged(seed=91)
