@@ -504,7 +504,8 @@ fka_status fka_read_probe(const void *buf, size_t bytes, int32_t blocks, int32_t
  * clamped, 2 = an append found no room (length at max_suffix_len or no page),
  * 4 = a page id outside the page table bounds was met, 8 = a merge record in
  * the plan's workspace pointed outside it (only if that memory was written from
- * outside the library; the record was not followed). */
+ * outside the library; the record was not followed), or the suffix lengths of an
+ * instruction prefill shrank while it ran (some suffix keys were left out). */
 fka_status fka_plan_device_error(const fka_plan *plan, int32_t *flags);
 
 /* Release a plan and its device memory.  NULL is ignored. */

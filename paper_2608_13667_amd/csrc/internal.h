@@ -153,6 +153,24 @@ __host__ inline ExactDiv exact_div(int64_t d)
 }
 __host__ __device__ inline int32_t operator/(int32_t x, ExactDiv d) { return (int32_t)(((uint64_t)(uint32_t)x * d.m) >> d.s); }
 
+// The tiled prefill's tail counts its groups branch by branch, 64 branches (a chunk) at a time.  Finds the
+// chunk that holds group idx: from the chunk whose first branch is `first`, which `base` groups precede,
+// chunk by chunk up to branch `last`.  total() is the present chunk's groups, load(b) takes the chunk that
+// starts at branch b.  False where no chunk is left: each one is read again here, so the lengths may no
+// longer be those that idx was counted from.
+template <class Total, class Load>
+__host__ __device__ __attribute__((always_inline)) inline bool find_chunk(int32_t idx, int32_t last, int32_t &first,
+                                                                          int32_t &base, Total &&total, Load &&load)
+{
+    while (idx - base >= total()) {
+        if (last - first < 64) return false;
+        base += total();
+        first += 64;
+        load(first);
+    }
+    return true;
+}
+
 // The tiled prefill's divisors, and what its split divides for good (fixed by the plan).
 struct TileSplit {
     ExactDiv kv_heads, unit_groups, ranges, group, branch_rows;  // branch_rows: tokens x G

@@ -490,13 +490,10 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
             pos = GRP * idx;
             limit = Lp - tail0 - 1 - pos;
             rows_ok = min(GRP, limit + 1);
-        } else if (idx < n_groups) {
-            int k = idx - br_base;
-            while (k >= __builtin_amdgcn_readlane(br_scan, 63)) {  // the next chunk of branches
-                br_base += __builtin_amdgcn_readlane(br_scan, 63);
-                k = idx - br_base;
-                take_branches(br_first + 64, request_branches(br_first + 64));
-            }
+        } else if (idx < n_groups &&
+                   find_chunk(idx, br_z, br_first, br_base, [&]() INLINE { return __builtin_amdgcn_readlane(br_scan, 63); },
+                              [&](int first) INLINE { take_branches(first, request_branches(first)); })) {
+            const int k = idx - br_base;
             const int i = uni(__builtin_ctzll(__builtin_amdgcn_ballot_w64(br_scan > k)));
             b = br_first + i;
             const int L = __builtin_amdgcn_readlane(br_len, i);
@@ -504,6 +501,8 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
             pos = GRP * (k - (__builtin_amdgcn_readlane(br_scan, i) - (keys + GRP - 1) / GRP));
             limit = L - pos;
             rows_ok = min(GRP, keys - pos);
+        } else if (idx < n_groups && lane == 0) {
+            atomicOr(a.err, kErrBadSchedule);  // the lengths shrank while the kernel read them: the group is left out
         }
         size_t off = 0;
         if (rows_ok > 0) {

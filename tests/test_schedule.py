@@ -36,3 +36,13 @@ def test_even_split_matches_the_general_split():
                        check=True, capture_output=True, cwd=d)
         r = subprocess.run([exe, "3000"], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+
+
+def test_tail_groups_are_found_in_bounded_steps():
+    with tempfile.TemporaryDirectory() as d:
+        exe = os.path.join(d, "find_chunk_check")
+        subprocess.run([_hipcc(), "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2608_13667_amd", "csrc"),
+                        os.path.join(ROOT, "tests", "native", "find_chunk_check.cpp"), "-o", exe],
+                       check=True, capture_output=True, cwd=d)
+        r = subprocess.run([exe, "500"], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
