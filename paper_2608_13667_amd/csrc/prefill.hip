@@ -72,7 +72,8 @@ constexpr int NW = 8;              // waves per block (two per SIMD)
 constexpr int STAGES = 4;          // prefix tile buffers: two read, two loading
 constexpr int GRP = 8;             // keys per group of a tail tile (what one wave loads of a tile)
 constexpr float kLn2 = 0.693147180559945309f;
-constexpr float kRescaleLimit = 256.f;  // a lane's sum of p over a tile past which its rows' references move
+constexpr float kRescaleLimit = 256.f;  // a lane's sum of a row's p over a tile past which the row's reference moves
+constexpr float kNoKey = 3.402823466e38f;  // minus the reference of a row without keys: the largest float
 
 static_assert(STAGES == 4, "the tile loop is unrolled over its four buffers");
 
@@ -552,10 +553,10 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
 
     // ---- online softmax state: lane owns unit rows l16 (t = 0) and 16 + l16 (t = 1).  nm is minus
     // the row's reference in log2 units, the maximum of the scores that last moved it: p = 2^(score -
-    // reference), sums and accumulator are relative to it.  +inf before the row's first key: p is then
-    // inf or NaN, which sends the tile to the path that sets a reference.
+    // reference), sums and accumulator are relative to it.  The lowest number before the row's first
+    // key: p of a key is then past every limit and p of a masked one 0.
     f32x4 acc[2][NE];
-    float nm[2] = {INFINITY, INFINITY}, l_run[2] = {0.f, 0.f};
+    float nm[2] = {kNoKey, kNoKey}, l_run[2] = {0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -581,35 +582,40 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
             sum[t] = (ps[0] + ps[1]) + (ps[2] + ps[3]);
         }
     };
-    // The references moved to the tile's maxima where these are higher, sums and accumulator rescaled.
-    auto move_reference = [&](const float (&x)[2][4 * MT], float (&r)[2]) INLINE {
+    // The references of the rows whose sum is past the limit in any of their four lanes moved to the tile's
+    // maxima, sums and accumulator rescaled.  The other rows of the unit are left as they are, alpha 1 and
+    // the same p, so that a row's bits do not depend on what the rows beside it hold.
+    auto move_reference = [&](const float (&x)[2][4 * MT], const float (&sum)[2]) INLINE {
         float mx[2] = {max_of(x[0]), max_of(x[1])};
         max_over_rows2(mx[0], mx[1]);
         xdl_result_wait();
+        const int row = opaque_lane_id() & 15;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
+            uint64_t over = __builtin_amdgcn_ballot_w64(sum[t] > kRescaleLimit);
+            over |= over >> 32;
+            over |= over >> 16;
             const float m_new = mx[t] * a.scale_log2;  // the scale is positive: the order is kept
-            const bool move = m_new > -nm[t];
-            // alpha: exactly 1 for a row that keeps its reference, 0 for a row's first keys
-            const float alpha = !move ? 1.f : nm[t] == INFINITY ? 0.f : fast_exp2(-nm[t] - m_new);
+            const bool move = ((uint32_t)over >> row & 1) != 0 && m_new > -nm[t];
+            const float alpha = move ? fast_exp2(-nm[t] - m_new) : 1.f;  // 0 for a row's first keys
             l_run[t] *= alpha;
 #pragma unroll
             for (int e = 0; e < NE; ++e) acc[t][e] *= alpha;
             nm[t] = move ? -m_new : nm[t];
-            r[t] = nm[t] == INFINITY ? 0.f : nm[t];  // no key so far: every score is -inf
         }
     };
     // A tile's softmax.  Any reference gives the same result while nothing overflows (all that it
-    // scales is in fp32), so p is taken against the old one and only a lane's sum past kRescaleLimit
-    // (or NaN) leads to the path with the maxima: a maximum per tile costs 26 of 250 vector issue
-    // slots, and beside a matrix wave those bound the step.
-    auto softmax = [&](const float (&x)[2][4 * MT], bf16x8 (&ph)[2][KS], bf16x8 (&pl)[2][KS]) INLINE {
-        float sum[2];
-        exps(x, nm, ph, pl, sum);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(sum[0] + sum[1] <= kRescaleLimit)) != 0, 0)) {
-            float r[2];
-            move_reference(x, r);
-            exps(x, r, ph, pl, sum);
+    // scales is in fp32), so p is taken against the old one and only a row whose sum in a lane is past
+    // kRescaleLimit leads to the path with the maxima: a maximum per tile costs 26 of 250 vector issue
+    // slots, and beside a matrix wave those bound the step.  (A NaN row stays on the path without: the
+    // larger of two sums, one of them NaN, is the other.)
+    // `first`: the range's first tile, where every row with a key takes its reference.
+    auto softmax = [&](const float (&x)[2][4 * MT], bf16x8 (&ph)[2][KS], bf16x8 (&pl)[2][KS], bool first) INLINE {
+        float sum[2] = {INFINITY, INFINITY};
+        if (!first) exps(x, nm, ph, pl, sum);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(fmaxf(sum[0], sum[1]) > kRescaleLimit) != 0, 0)) {
+            move_reference(x, sum);
+            exps(x, nm, ph, pl, sum);
         }
         l_run[0] += sum[0];
         l_run[1] += sum[1];
@@ -715,7 +721,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int i = 0; i < 4 * MT; ++i) x[t][i] = sc[t][i >> 2][i & 3];
-        softmax(x, ph, pl);
+        softmax(x, ph, pl, false);
     };
     f32x4 sc[2][MT];
     bf16x8 ph[2][KS], pl[2][KS];
@@ -801,7 +807,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         }
         if (use) matrix(std::false_type{}, zero{}, zero{}, (uint32_t)(i % STAGES) * KBYTES, 0u, sc, ph, pl);
     };
-    auto any_sm = [&]() INLINE {
+    auto any_sm = [&](int i) INLINE {
         if (!use) return;
         xdl_result_wait();
         float x[2][4 * MT];
@@ -811,7 +817,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
 #pragma unroll
             for (int i = 0; i < 4 * MT; ++i)
                 x[t][i] = (k0 + (i & 3) <= lim[t][i >> 2]) ? sc[t][i >> 2][i & 3] : -INFINITY;
-        softmax(x, ph, pl);
+        softmax(x, ph, pl, i == 0);
     };
     auto any_pv = [&](int i) INLINE {
         if (!use) return;
@@ -888,14 +894,14 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
             if constexpr (LEAD)
                 mat();
             else if (i > 0)
-                any_sm();
+                any_sm(i - 1);
         }
         lds_barrier();
         if (active) {
             if constexpr (!LEAD)
                 mat();
             else if (i < ntot)
-                any_sm();
+                any_sm(i);
         }
     };
     // Step i between two whole tiles, with the buffers' offsets known at run time: what the unrolled

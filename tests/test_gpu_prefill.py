@@ -322,6 +322,32 @@ def test_prefill_tiled_nonfinite_instruction_value(fa):
     assert plan.device_error() == 0 and pplan.device_error() == 0
 
 
+@pytest.mark.parametrize("how", ["climbing", "nan"])
+@pytest.mark.parametrize("d,blocks", [(128, 0), (128, 2), (64, 0), (64, 2)])
+def test_prefill_tiled_rows_do_not_depend_on_other_branches(fa, d, blocks, how):
+    """A row's bits depend on its own query and keys only: with branch 1's queries replaced (scores that
+    are 30 times as large and climb past every reference, or one NaN query row), the rows of the other
+    branches are bit for bit the same, those that share a 32-row unit with branch 1 among them (80 rows
+    per branch and KV head); by the plan's ranges and with an explicit grid of one range (23 whole
+    tiles), contiguous and paged."""
+    n = 20
+    w = W.make(W.CONFIGS["mid"].replace(head_dim=d, n_kv_heads=2, n_q_heads=8, n_branches=4, prefix_len=1509,
+                                        suffix_range=(3, 40), steps=n, seed=2771))
+    q, sk, sv = _instruction(w, n)
+    other = q.copy()
+    if how == "climbing":
+        other[1] = W.bf16_bits(W.bf16_to_f32(q[1]) * np.float32(30.0))
+    else:
+        other[1, n // 2] = W.BF16_NAN
+    keep = [t for t in range(4 * n) if t // n != 1]
+    for run in (lambda x: _run(fa, w, n, x, sk, sv, blocks=blocks),
+                lambda x: _run_paged(fa, w, n, x, sk, sv, seed=2772, blocks=blocks)):
+        plan, out, lse = run(q)
+        assert plan.info().units_per_block == 8 and (plan.info().n_slots == 1) == (blocks > 0)
+        _, out2, lse2 = run(other)
+        assert np.array_equal(out[keep], out2[keep]) and np.array_equal(lse[keep], lse2[keep])
+
+
 def test_prefill_paired_units_on_the_streaming_path(fa):
     """Fewer than 256 rows per KV head keeps the partial kernel's prefill instantiation; with 64 KV
     heads its items (5 units of 32 rows x 64) outnumber the resident blocks, so an eight-wave block
