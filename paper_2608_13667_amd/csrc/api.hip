@@ -590,7 +590,8 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
         // 2 KV heads, 320 rows 9 tiles 16.0 / 18.0 / 20.1; on the other side of the line 320 rows 78 tiles
         // 25.9 / 23.4 / 23.3, 240 rows 128 tiles 28.5 / 27.1 / 27.9.  A tile to a range is no faster (two steps again).
         const int64_t two = (2 * PT + 2) / 3, three = (2 * PT + 4) / 5;
-        R = std::min<int64_t>(R, std::max<int64_t>(1, two * U * p->d <= 28000 ? two : three));
+        // A caller's grid is cut as finely as it asks for, down to a tile to a range.
+        R = std::min<int64_t>(R, std::max<int64_t>(1, blocks > 0 ? PT : two * U * p->d <= 28000 ? two : three));
         // the partials of one range: S Hq rows of d floats; the ranges together stay below 256 MiB
         const int64_t range_bytes = S * p->Hq * (int64_t)p->d * 4;
         R = std::max<int64_t>(1, std::min<int64_t>(R, ((int64_t)256 << 20) / range_bytes));

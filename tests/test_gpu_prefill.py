@@ -296,6 +296,23 @@ def test_prefill_kernel_choice(fa, c, tiled):
         assert p.device_error() == 0
 
 
+@pytest.mark.parametrize("blocks,ranges", [(92, 23), (60, 15), (4, 1), (1000, 23)])
+def test_prefill_tiled_explicit_grid(fa, blocks, ranges):
+    """A caller's grid is followed down to one whole tile per range (23 of them here, 4 blocks per range),
+    also where the plan's own choice would take longer ranges; every row checked, contiguous and paged."""
+    n = 20
+    w = W.make(W.CONFIGS["mid"].replace(n_kv_heads=2, n_q_heads=8, n_branches=4, prefix_len=1509, suffix_range=(3, 40),
+                                        steps=n, seed=2773))
+    q, sk, sv = _instruction(w, n)
+    ref, ref_lse = _reference(w, n, q, sk, sv)
+    for what, (plan, out, lse) in (("contiguous", _run(fa, w, n, q, sk, sv, blocks=blocks)),
+                                   ("paged", _run_paged(fa, w, n, q, sk, sv, seed=2774, blocks=blocks))):
+        assert plan.info().units_per_block == 8 and plan.info().n_slots == ranges
+        gates.assert_gates(out, ref, what=f"{blocks} blocks, {what}")
+        gates.assert_lse(lse, ref_lse, what=f"{blocks} blocks, {what}")
+        assert plan.device_error() == 0
+
+
 def test_prefill_tiled_nonfinite_instruction_value(fa):
     """A NaN in the value of instruction token 17 of branch 1 (KV head 1) reaches exactly the rows
     that attend to it: branch 1's tokens 17.. on that KV head's query heads.  Its earlier tokens and
