@@ -34,7 +34,7 @@
 //     branch the block's rows belong to -- form tiles of eight 8-key groups, each group of one branch,
 //     which go through the same buffers; each row is masked to its own branch and causal limit.
 //     The ranges share these tiles like the others (their number follows from the suffix lengths
-//     on the device).  A non-finite value there is replaced by zero for the product and the rows
+//     on the device).  A non-finite value of a suffix is replaced by zero for the product and the rows
 //     that read its key are made NaN, so that it reaches no row of another branch or of an earlier
 //     token.
 // What bounds it: beside a wave that issues matrix products at full rate the other wave of the SIMD
@@ -768,6 +768,7 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
     // A lane's four keys of score tile i are keys 4 (q4 mod 2) + j of group 2 i + q4 / 2.
     bool use = true, tail = false;
     int lim[2][MT];  // row t reads the keys k <= lim[t][i] of group 2 i + q4 / 2
+    uint32_t suffix_groups = 0;  // bit i: that group holds suffix keys (not the prefix's, which every row reads)
 #pragma unroll
     for (int i = 0; i < MT; ++i) lim[0][i] = lim[1][i] = KT;
     int row_bt[2];  // the rows' branch (past every branch beyond the head's rows) << 16 | token
@@ -794,9 +795,11 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
 #pragma unroll
             for (int q = 0; q < MT; ++q) asm volatile("" : "+v"(d[q]));
             int most = -1;
+            suffix_groups = 0;
 #pragma unroll
             for (int q = 0; q < MT; ++q) {
                 const int b = (int)(uint32_t)d[q], base = (int)(d[q] >> 32);
+                suffix_groups |= b >= 0 ? 1u << q : 0;
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     lim[t][q] = b == -1 ? base : b == row_bt[t] >> 16 ? base + (row_bt[t] & 0xffff) : -1;
@@ -832,9 +835,10 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
             lds_wait();
             static_for<GS>([&](auto Gc) INLINE { tie_v(v[decltype(Gc)::value]); });
             if (tail) {
-                // A non-finite value of a group is zeroed for the product and the rows that read its key
-                // are made NaN (through their sums), so that it reaches no row of another branch or of
-                // an earlier token (a masked row's p is 0, and 0 times such a value would be NaN).
+                // A non-finite value of a suffix group is zeroed for the product and the rows that read its
+                // key are made NaN (through their sums), so that it reaches no row of another branch or of
+                // an earlier token (a masked row's p is 0, and 0 times such a value would be NaN).  The
+                // prefix's keys are read by every row: theirs stay in the product, as in the whole tiles.
                 uint32_t bits = 0;
 #pragma unroll
                 for (int e = 0; e < PG; ++e)
@@ -849,13 +853,15 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
                     const int k0 = 4 * ((opaque_lane_id() >> 4) & 1);
 #pragma unroll
                     for (int y = 0; y < 2; ++y) {
+                        // the exponent bits that count as non-finite (none for the prefix's keys)
+                        const uint32_t bad = (suffix_groups >> (2 * kk + y) & 1) ? 0x7f80u : ~0u;
                         int first = 0x7fffffff;
 #pragma unroll
                         for (int e = 0; e < PG; ++e) {
                             uint64_t w = (uint64_t)v[e / EG][e % EG][y];
 #pragma unroll
                             for (int k = 0; k < 4; ++k)
-                                if (((uint32_t)(w >> (16 * k)) & 0x7f80u) == 0x7f80u) {
+                                if (((uint32_t)(w >> (16 * k)) & 0x7f80u) == bad) {
                                     first = min(first, k0 + k);
                                     w &= ~((uint64_t)0xffffu << (16 * k));
                                 }

@@ -339,6 +339,28 @@ def test_prefill_tiled_nonfinite_instruction_value(fa):
     assert plan.device_error() == 0 and pplan.device_error() == 0
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("pos", [200, 896, 899], ids=["whole-tile", "first-past-the-tiles", "last"])
+def test_prefill_tiled_nan_prefix_value(fa, d, pos):
+    """A NaN in one channel of a prefix value reaches that channel of every row of its KV head and nothing
+    else, whether the key lies in a whole 64-key tile or among the last 900 mod 64 keys, which share
+    their tile with suffix keys; contiguous and paged."""
+    n, hkv, G = 20, 2, 5
+    w = W.make(W.CONFIGS["mid"].replace(head_dim=d, n_kv_heads=hkv, n_q_heads=hkv * G, n_branches=3, prefix_len=900,
+                                        suffix_range=(3, 30), steps=n, seed=2775))
+    q, sk, sv = _instruction(w, n)
+    ref, ref_lse = _reference(w, n, q, sk, sv)
+    w.prefix_v[1, pos, 5] = W.BF16_NAN
+    hit = np.zeros(ref.shape, bool)
+    hit[:, G:, 5] = True
+    for what, (plan, out, lse) in (("contiguous", _run(fa, w, n, q, sk, sv)),
+                                   ("paged", _run_paged(fa, w, n, q, sk, sv, seed=2776))):
+        assert plan.info().units_per_block == 8
+        assert np.all(np.isnan(out[hit])) and not np.any(np.isnan(out[~hit])), what
+        gates.assert_gates(np.where(hit, 0, out), np.where(hit, 0, ref), what=what)
+        gates.assert_lse(lse, ref_lse, what=what)
+
+
 @pytest.mark.parametrize("how", ["climbing", "nan"])
 @pytest.mark.parametrize("d,blocks", [(128, 0), (128, 2), (64, 0), (64, 2)])
 def test_prefill_tiled_rows_do_not_depend_on_other_branches(fa, d, blocks, how):
