@@ -28,7 +28,7 @@ struct fka_plan {
     // instruction prefill on the tiled kernel: 32-row units per KV head, blocks of
     // eight units, key ranges, whole prefix tiles of 64 keys
     bool prefill_tiles = false;
-    int32_t tile_units = 0, tile_unit_groups = 0, tile_ranges = 0, tile_prefix = 0;
+    int32_t tile_units = 0, tile_unit_groups = 0, tile_ranges = 0, tile_prefix_ranges = 0, tile_prefix = 0;
     fka::TileSplit tile_split{};
     int32_t max_suffix_len = 0;
     // contiguous
@@ -443,6 +443,7 @@ fka_status run_prefill(const fka_plan *p, const fka::AttnArgs &a, float *out, fl
         t.n_units = p->tile_units;
         t.unit_groups = p->tile_unit_groups;
         t.ranges = p->tile_ranges;
+        t.prefix_ranges = p->tile_prefix_ranges;
         t.prefix_tiles = p->tile_prefix;
         t.split = p->tile_split;
         t.scale_log2 = p->scale * 1.4426950408889634f;
@@ -590,18 +591,36 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
         // 2 KV heads, 320 rows 9 tiles 16.0 / 18.0 / 20.1; on the other side of the line 320 rows 78 tiles
         // 25.9 / 23.4 / 23.3, 240 rows 128 tiles 28.5 / 27.1 / 27.9.  A tile to a range is no faster (two steps again).
         const int64_t two = (2 * PT + 2) / 3, three = (2 * PT + 4) / 5;
-        // A caller's grid is cut as finely as it asks for, down to a tile to a range.
-        R = std::min<int64_t>(R, std::max<int64_t>(1, blocks > 0 ? PT : two * U * p->d <= 28000 ? two : three));
+        int64_t RP = std::min<int64_t>(R, std::max<int64_t>(1, two * U * p->d <= 28000 ? two : three));
+        // Further ranges for the tail, by its tiles at the longest suffixes: four tiles to a range, up to 64
+        // ranges.  The lengths are known on the device only; where the suffixes are short these ranges stay
+        // empty and cost each row an empty part, and without them a long tail runs on as many blocks as the
+        // prefix has.  Measured (us, suffixes empty / full; ranges of the prefix only against these): d 128, 8 KV heads, 40 prefix keys,
+        // one token over 4096 11.2 / 164 against 10.8 / 14.4, 4 x 4 over 2048 each 13.4 / 328 against 12.5 / 23.4; 600 keys, 64 x 1 (G 1)
+        // over 1024 15.1 / 431 against 13.5 / 92; 1 KV head, 600 keys, 5 x 4 over 4096 15.0 / 155 against 14.9 / 25.5 (128 ranges
+        // 16.1 / 19.3, 256 17.7 / 18.3: the empty parts then cost more than a server's short suffixes are worth).
+        const int64_t block_rows = (int64_t)ceil_div(U, UG) * tile_rows, branch_rows = (int64_t)n * G;
+        const int64_t block_branches = std::min<int64_t>(N, (block_rows - 1) / branch_rows + 2);
+        const int64_t keys_tiles = PT + (ceil_div(Lp % 64, 8) + block_branches * ceil_div(max_suffix_len, 8) + 7) / 8;
+        if (blocks > 0) {  // a caller's grid is cut as finely as it asks for, down to a tile to a range
+            R = std::min<int64_t>(R, std::max<int64_t>(1, keys_tiles));
+            RP = std::min<int64_t>(R, std::max(1, PT));
+        } else {
+            R = std::max(RP, std::min<int64_t>(R, std::min<int64_t>(64, (keys_tiles + 3) / 4)));
+        }
         // the partials of one range: S Hq rows of d floats; the ranges together stay below 256 MiB
         const int64_t range_bytes = S * p->Hq * (int64_t)p->d * 4;
         R = std::max<int64_t>(1, std::min<int64_t>(R, ((int64_t)256 << 20) / range_bytes));
+        RP = std::min(R, RP);
         p->prefill_tiles = true;
         p->tile_units = U;
         p->tile_unit_groups = UG;
         p->tile_ranges = (int32_t)R;
+        p->tile_prefix_ranges = (int32_t)RP;
         p->tile_prefix = PT;
         p->tile_split = fka::TileSplit{fka::exact_div(p->Hkv), fka::exact_div(UG), fka::exact_div(R), fka::exact_div(G),
-                                       fka::exact_div((int64_t)n * G), U / UG, U % UG, PT / (int32_t)R, PT % (int32_t)R};
+                                       fka::exact_div((int64_t)n * G), fka::exact_div(std::max<int64_t>(1, R - RP)), U / UG, U % UG,
+                                       PT / (int32_t)RP, PT % (int32_t)RP};
         for (int32_t u = 0; u < U; ++u) {
             fka::UnitRec r{};
             r.seq0 = (int32_t)(((int64_t)u * tile_rows) / G);

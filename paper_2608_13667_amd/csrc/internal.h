@@ -174,9 +174,34 @@ __host__ __device__ __attribute__((always_inline)) inline bool find_chunk(int32_
 // The tiled prefill's divisors, and what its split divides for good (fixed by the plan).
 struct TileSplit {
     ExactDiv kv_heads, unit_groups, ranges, group, branch_rows;  // branch_rows: tokens x G
+    ExactDiv extra;                  // ranges without prefix tiles (1 if none)
     int32_t units_each, units_more;  // units / unit groups, remainder
-    int32_t pre_each, pre_more;      // prefix tiles / ranges, remainder
+    int32_t pre_each, pre_more;      // prefix tiles / prefix ranges, remainder
 };
+
+// The tail tiles [t0, t0 + n) of range r of R, of which the first RP have the prefix's tiles (s.pre_each, the
+// first s.pre_more of them one more).  The ranges without any take tail tiles up to pre_each of them (they
+// stay empty where the suffixes are short); what is left is dealt to all, first to the ranges without a spare
+// prefix tile.  No range has more tiles than the fairest split or the prefix gives it.
+__host__ __device__ inline void tail_share(const TileSplit &s, int32_t RP, int32_t R, int32_t tail_tiles, int32_t r, int32_t &t0,
+                                           int32_t &n)
+{
+    const int32_t pos = r >= s.pre_more ? r - s.pre_more : r - s.pre_more + R, first = RP - s.pre_more, extra = R - RP;
+    const int32_t in_extra = pos < first ? 0 : pos < R - s.pre_more ? pos - first : extra;  // such ranges in front of this one
+    const int32_t left = tail_tiles - extra * s.pre_each;
+    int32_t each, more;
+    if (left <= 0) {
+        each = tail_tiles / s.extra;
+        more = tail_tiles - each * extra;
+        t0 = in_extra * each + (in_extra < more ? in_extra : more);
+        n = r >= RP ? each + (in_extra < more ? 1 : 0) : 0;
+    } else {
+        each = left / s.ranges;
+        more = left - each * R;
+        t0 = pos * each + (pos < more ? pos : more) + in_extra * s.pre_each;
+        n = each + (pos < more ? 1 : 0) + (r >= RP ? s.pre_each : 0);
+    }
+}
 
 struct AttnArgs {
     const UnitRec *units;  // [n_units]
@@ -331,6 +356,7 @@ struct PrefillArgs {
     int32_t n_units;       // 32-row units per KV head
     int32_t unit_groups;   // ceil(n_units / 8)
     int32_t ranges;        // R
+    int32_t prefix_ranges; // of these, the first that have the prefix's whole tiles
     int32_t prefix_tiles;  // floor(Lp / 64): whole 64-key tiles
     float scale_log2;      // softmax scale * log2(e)
     TileSplit split;

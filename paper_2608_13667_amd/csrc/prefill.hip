@@ -358,17 +358,16 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
     const int unit_z = unit_a + a.split.units_each + (ug < a.split.units_more ? 1 : 0);
     const int u = unit_a + wave;
     const bool active = u < unit_z;
-    const int R = a.ranges;
+    const int R = a.ranges, RP = a.prefix_ranges;
     const int PT = a.prefix_tiles;
 
     // ---- the block's keys: the prefix's whole tiles, then the tail -- the prefix's last Lp mod 64 keys
     // (every row reads them) and the suffix keys of the branches its rows belong to, each branch up
     // to the last key any of the block's rows reads -- in groups of eight keys, eight groups to a tile.
-    // The ranges share both: range r takes the prefix's tiles [s0, s0 + nmain) (known from the plan, so
-    // their loads do not wait for the suffix lengths) and tail tiles [tail_t0, + its share), the
-    // first spare tail tile going to the first range without a spare prefix tile.
+    // The first RP ranges share the prefix: range r takes its tiles [s0, s0 + nmain) (known from the plan,
+    // so their loads do not wait for the suffix lengths).  All R take tail tiles, as below.
     const int pre_each = a.split.pre_each, pre_more = a.split.pre_more;
-    const int s0 = r * pre_each + min(r, pre_more), nmain = pre_each + (r < pre_more ? 1 : 0);
+    const int s0 = r * pre_each + min(r, pre_more), nmain = r < RP ? pre_each + (r < pre_more ? 1 : 0) : 0;
 
     const int row_z = min(rows_head, unit_z * 32);
     const int br_a = (unit_a * 32) / a.split.branch_rows;
@@ -534,10 +533,9 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         }
         take_branches(br_a, request_branches(br_a));
     }
-    const int tail_tiles = (n_groups + NW - 1) / NW, tail_each = tail_tiles / a.split.ranges, tail_more = tail_tiles - tail_each * R;
-    const int tail_pos = r >= pre_more ? r - pre_more : r - pre_more + R;
-    const int tail_t0 = tail_pos * tail_each + min(tail_pos, tail_more);
-    const int ntot = nmain + tail_each + (tail_pos < tail_more ? 1 : 0);
+    int tail_t0, tail_n;
+    tail_share(a.split, RP, R, (n_groups + NW - 1) / NW, r, tail_t0, tail_n);
+    const int ntot = nmain + tail_n;
     // paged: the page ids of the next n tiles from the range's tile i are in page_ids
     auto have_pages = [&](int i, int n) INLINE {
         if constexpr (PAGED)
@@ -978,13 +976,14 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
         if (lr >= rows_head) continue;
         const int s = lr / a.split.group, h = g * G + lr - s * G;
         const size_t orow = (size_t)r * rows_total + (size_t)s * Hq + h;
-        // a row with no keys in this range: o = 0, lse = -inf (weight 0 in the merge)
+        // a row with no keys in this range: lse = -inf (the merge takes nothing of its o)
         const bool empty = !(l > 0.f) && !(l != l);
-        const float inv = empty ? 0.f : 1.f / l;
+        if (q4c == 0) a.part_lse[orow] = empty ? -INFINITY : (__log2f(l) - nm[t]) * kLn2;
+        if (empty) continue;
+        const float inv = 1.f / l;
         float *dst = a.part_o + orow * HD + 4 * q4c;
 #pragma unroll
         for (int e = 0; e < NE; ++e) *reinterpret_cast<f32x4 *>(dst + 16 * e) = acc[t][e] * inv;
-        if (q4c == 0) a.part_lse[orow] = empty ? -INFINITY : (__log2f(l) - nm[t]) * kLn2;
     }
 }
 

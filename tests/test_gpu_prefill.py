@@ -298,8 +298,9 @@ def test_prefill_kernel_choice(fa, c, tiled):
 
 @pytest.mark.parametrize("blocks,ranges", [(92, 23), (60, 15), (4, 1), (1000, 23)])
 def test_prefill_tiled_explicit_grid(fa, blocks, ranges):
-    """A caller's grid is followed down to one whole tile per range (23 of them here, 4 blocks per range),
-    also where the plan's own choice would take longer ranges; every row checked, contiguous and paged."""
+    """A caller's grid is followed down to a tile per range (23 whole ones here and those of the longest
+    suffixes, 4 blocks per range), also where the plan's own choice would take longer ranges; every row
+    checked, contiguous and paged."""
     n = 20
     w = W.make(W.CONFIGS["mid"].replace(n_kv_heads=2, n_q_heads=8, n_branches=4, prefix_len=1509, suffix_range=(3, 40),
                                         steps=n, seed=2773))
@@ -307,7 +308,8 @@ def test_prefill_tiled_explicit_grid(fa, blocks, ranges):
     ref, ref_lse = _reference(w, n, q, sk, sv)
     for what, (plan, out, lse) in (("contiguous", _run(fa, w, n, q, sk, sv, blocks=blocks)),
                                    ("paged", _run_paged(fa, w, n, q, sk, sv, seed=2774, blocks=blocks))):
-        assert plan.info().units_per_block == 8 and plan.info().n_slots == ranges
+        assert plan.info().units_per_block == 8
+        assert ranges <= plan.info().n_slots <= (ranges if blocks < 1000 else blocks // 4)
         gates.assert_gates(out, ref, what=f"{blocks} blocks, {what}")
         gates.assert_lse(lse, ref_lse, what=f"{blocks} blocks, {what}")
         assert plan.device_error() == 0
@@ -409,6 +411,32 @@ def test_prefill_paired_units_on_the_streaming_path(fa):
     assert pplan.info().units_per_block == 2
     gates.assert_gates(pout, ref, what="paired units, streaming, paged")
     assert plan.device_error() == 0 and pplan.device_error() == 0
+
+
+@pytest.mark.parametrize("c,lens", [
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=4, n=4, prefix_len=40, suffix_range=(1990, 1990)), None),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=4, n=4, prefix_len=200, suffix_range=(1500, 1500)), (0, 1, 1500, 77)),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=4, n=4, prefix_len=200, suffix_range=(1500, 1500)), (0, 0, 0, 0)),
+    (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=1, n=60, prefix_len=0, suffix_range=(2100, 2100)), None),
+    (dict(head_dim=64, n_kv_heads=2, n_q_heads=2, n_branches=80, n=1, prefix_len=300, suffix_range=(300, 300)), None),
+    (dict(head_dim=64, n_kv_heads=4, n_q_heads=28, n_branches=3, n=20, prefix_len=600, suffix_range=(900, 900)), (900, 0, 333)),
+], ids=["long", "one-long", "empty", "no-prefix", "80-branches-d64", "mixed-d64"])
+def test_prefill_tiled_long_suffixes(fa, c, lens):
+    """Suffixes longer than the prefix (up to 2100 keys over 0-600): the plan adds ranges for them, which share the
+    tail with those of the prefix and stay empty where the suffixes turn out short.  Every row checked,
+    contiguous and paged."""
+    n = c["n"]
+    w = W.make(W.CONFIGS["mid"].replace(**{k: v for k, v in c.items() if k != "n"}, steps=n, seed=2777))
+    if lens is not None:
+        w.suffix_len[:] = lens
+    q, sk, sv = _instruction(w, n)
+    ref, ref_lse = _reference(w, n, q, sk, sv)
+    for what, (plan, out, lse) in (("contiguous", _run(fa, w, n, q, sk, sv)), ("paged", _run_paged(fa, w, n, q, sk, sv, seed=2778))):
+        info = plan.info()
+        assert info.units_per_block == 8 and info.n_slots > max(1, c["prefix_len"] // 64)
+        gates.assert_gates(out, ref, what=f"{c}, {what}")
+        gates.assert_lse(lse, ref_lse, what=f"{c}, {what}")
+        assert plan.device_error() == 0
 
 
 def _tiled_case(seed, n=20):

@@ -46,3 +46,13 @@ def test_tail_groups_are_found_in_bounded_steps():
                        check=True, capture_output=True, cwd=d)
         r = subprocess.run([exe, "500"], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+
+
+def test_tail_share_covers_the_tail_once():
+    with tempfile.TemporaryDirectory() as d:
+        exe = os.path.join(d, "tail_share_check")
+        subprocess.run([_hipcc(), "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2608_13667_amd", "csrc"),
+                        os.path.join(ROOT, "tests", "native", "tail_share_check.cpp"), "-o", exe],
+                       check=True, capture_output=True, cwd=d)
+        r = subprocess.run([exe, "3000"], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
