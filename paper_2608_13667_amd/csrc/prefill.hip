@@ -969,9 +969,56 @@ __device__ INLINE inline void prefill_tiles(const PrefillArgs &a)
     const int l16c = lane_c & 15, q4c = lane_c >> 4;
     const size_t rows_total = (size_t)S * Hq;
     xdl_result_wait();
+    // An infinite value of the prefix meets hi and lo of p one after the other, and lo has either sign: inf - inf
+    // for about half of the rows, where the result is that infinity.  So where a row with a finite sum has
+    // a non-finite channel (products of pairs tell at 16 steps a row), the channel's values are looked up.
+    bool wrong = false;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        const float l = sum_over_rows(l_run[t]);
+        l_run[t] = sum_over_rows(l_run[t]);
+        float x = 0.f;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            x = __builtin_fmaf(acc[t][e][0], acc[t][e][1], x);
+            x = __builtin_fmaf(acc[t][e][2], acc[t][e][3], x);
+        }
+        wrong |= l_run[t] < INFINITY && !(__builtin_fabsf(x) < INFINITY);
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(wrong) != 0, 0)) {
+        // lane l looks at channels CL l .. of the range's prefix keys; bits 3 i of `seen` channel CL l + i: +inf, -inf, NaN
+        constexpr int CL = HD / 64;
+        uint32_t seen = 0;
+        auto look = [&](int k_a, int k_z) INLINE {
+            for (int k = k_a; k < k_z; ++k) {
+                const char *row = pv + ((size_t)g * Lp + k) * ROWB;
+                if constexpr (PAGED) {
+                    const int32_t page = scalar_load(a.page_table + uni(min(k / kPageSize, a.max_pages - 1)));
+                    if (page < 0 || page >= a.n_pool_pages) continue;
+                    row = pv + (((size_t)page * Hkv + g) * kPageSize + k % kPageSize) * ROWB;
+                }
+#pragma unroll
+                for (int i = 0; i < CL; ++i) {
+                    const uint32_t x = reinterpret_cast<const uint16_t *>(row)[CL * lane_c + i];
+                    seen |= (x == 0x7f80u ? 1u : x == 0xff80u ? 2u : (x & 0x7fffu) > 0x7f80u ? 4u : 0u) << (3 * i);
+                }
+            }
+        };
+        look(s0 * KT, (s0 + nmain) * KT);
+        if (tail_t0 == 0 && ntot > nmain) look(tail0, Lp);  // (fewer than 64 keys: the first tail tile)
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int c = 16 * e + 4 * q4c + j;
+                const uint32_t f = (uint32_t)__shfl((int)seen, c / CL) >> (3 * (c % CL)) & 7u;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    if (l_run[t] < INFINITY && (f == 1 || f == 2)) acc[t][e][j] = f == 1 ? INFINITY : -INFINITY;
+            }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const float l = l_run[t];
         const int lr = u * 32 + 16 * t + l16c;
         if (lr >= rows_head) continue;
         const int s = lr / a.split.group, h = g * G + lr - s * G;

@@ -363,6 +363,30 @@ def test_prefill_tiled_nan_prefix_value(fa, d, pos):
         gates.assert_lse(lse, ref_lse, what=what)
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_tiled_infinite_prefix_value(fa, d):
+    """Infinite prefix values: a channel that holds infinities of one sign (in whole tiles, or among the last
+    900 mod 64 keys) is that infinity in every row of its KV head, a channel with both signs is NaN, and
+    nothing else changes; contiguous and paged."""
+    n, hkv, G = 20, 2, 5
+    w = W.make(W.CONFIGS["mid"].replace(head_dim=d, n_kv_heads=hkv, n_q_heads=hkv * G, n_branches=3, prefix_len=900,
+                                        suffix_range=(3, 30), steps=n, seed=2779))
+    q, sk, sv = _instruction(w, n)
+    ref, ref_lse = _reference(w, n, q, sk, sv)
+    pos, neg = 0x7f80, 0xff80
+    want = {0: np.inf, 5: -np.inf, d - 1: np.inf, 8: -np.inf, 9: np.nan}
+    for c, k, x in ((0, 200, pos), (0, 700, pos), (5, 333, neg), (d - 1, 897, pos), (8, 899, neg), (9, 64, pos), (9, 898, neg)):
+        w.prefix_v[1, k, c] = x
+    for what, (plan, out, lse) in (("contiguous", _run(fa, w, n, q, sk, sv)),
+                                   ("paged", _run_paged(fa, w, n, q, sk, sv, seed=2780))):
+        assert plan.info().units_per_block == 8
+        for c, x in want.items():
+            assert np.array_equal(out[:, G:, c], np.full_like(out[:, G:, c], x), equal_nan=True), (what, c)
+            out[:, G:, c] = ref[:, G:, c]
+        gates.assert_gates(out, ref, what=what)
+        gates.assert_lse(lse, ref_lse, what=what)
+
+
 @pytest.mark.parametrize("how", ["climbing", "nan"])
 @pytest.mark.parametrize("d,blocks", [(128, 0), (128, 2), (64, 0), (64, 2)])
 def test_prefill_tiled_rows_do_not_depend_on_other_branches(fa, d, blocks, how):
