@@ -427,8 +427,8 @@ def test_lse_merge_rows_per_block(fa, d, R, P):
 @pytest.mark.parametrize("d,P", [(128, 9), (128, 32), (128, 33), (128, 64), (128, 257), (128, 513), (64, 16), (64, 17), (64, 64),
                                  (64, 65), (64, 256), (64, 300)])
 def test_lse_merge_many_parts(fa, d, P):
-    """The merge of one row per block at the edges of its batches (1, 4 and 8 parts of 8 or 16 slices at a time,
-    64 and 256 lane-wise lse values), with empty parts whose o is NaN, a row without any key and a row
+    """The merge of one row per block at the edges of its batches (1, 4, and 8 parts at a time for each of 8
+    slices at d 128 or 16 at d 64), with empty parts whose o is NaN, a row without any key and a row
     with a NaN part, which becomes NaN."""
     R = 5 if P > 8 * 4 else 1500
     rng = np.random.default_rng(P)

@@ -88,8 +88,7 @@ def test_prefill_long_shape(fa, n):
 
 
 def _check_tiled_plan(info, n_kv_heads, rows_per_head):
-    """Head dim 128 with at least 256 rows per KV head runs the tiled kernel: 32-row units, eight
-    per block (one per wave), blocks =
+    """The plan of the tiled kernel: 32-row units, up to eight per block (one per wave), blocks =
     KV heads x unit groups x prefix ranges in one round of resident blocks, one partial slot per
     range (the KV head varies fastest in the grid, so with 8 KV heads a head's blocks share an XCD)."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
@@ -124,6 +123,29 @@ def test_prefill_random_shapes(fa, c):
     """Seeded shapes: d 64 / 128, 1..8 KV heads, G 1..8, 1..6 branches, 1..39 tokens, prefixes of
     0..3000 (some not a multiple of the 32-key slice), existing suffixes, explicit grids."""
     _check_case(fa, c)
+
+
+@pytest.mark.parametrize("blocks", [0, 7, 64, 300])
+@pytest.mark.parametrize("c", [dict(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=3, n=7, prefix_len=4801, lo=3, seed=2781),
+                               dict(head_dim=64, n_kv_heads=2, n_q_heads=14, n_branches=6, n=6, prefix_len=9001, lo=40, seed=2782),
+                               dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=5, n=4, prefix_len=2311, lo=50, seed=2783),
+                               dict(head_dim=128, n_kv_heads=2, n_q_heads=12, n_branches=4, n=13, prefix_len=3017, lo=11, seed=2784)],
+                         ids=["d64-1unit", "d64-8units", "d128-4units", "d128-10units"])
+def test_prefill_streaming_shapes(fa, c, blocks):
+    """The partial kernel's prefill instantiation at shapes that the plan gives it, d 64 and 128, odd
+    prefixes, existing suffixes, automatic and explicit grids; every row checked, contiguous and paged."""
+    n = c["n"]
+    w = W.make(W.CONFIGS["mid"].replace(head_dim=c["head_dim"], n_kv_heads=c["n_kv_heads"], n_q_heads=c["n_q_heads"],
+                                        n_branches=c["n_branches"], prefix_len=c["prefix_len"],
+                                        suffix_range=(c["lo"], c["lo"] + 30), steps=n, seed=c["seed"]))
+    q, sk, sv = _instruction(w, n)
+    ref, ref_lse = _reference(w, n, q, sk, sv)
+    for what, (plan, out, lse) in (("contiguous", _run(fa, w, n, q, sk, sv, blocks=blocks)),
+                                   ("paged", _run_paged(fa, w, n, q, sk, sv, seed=c["seed"] + 1, blocks=blocks))):
+        assert plan.info().units_per_block != 8
+        gates.assert_gates(out, ref, what=f"{c}, {blocks} blocks, {what}")
+        gates.assert_lse(lse, ref_lse, what=f"{c}, {blocks} blocks, {what}")
+        assert plan.device_error() == 0
 
 
 def test_prefill_harvest_into_the_main_context(fa):
@@ -203,7 +225,7 @@ def _check_case(fa, c):
                                       blocks=0, seed=2753)],
                          ids=["empty-prefix", "one-range", "16-branches-per-unit", "prefix-under-one-tile"])
 def test_prefill_tiled_edges(fa, c):
-    """The tiled kernel (at least 256 rows per KV head) with no prefix at all (the suffix keys
+    """The tiled kernel with no prefix at all (the suffix keys
     only), with an explicit grid of one prefix range, with G = 1 and 2-token instructions of
     256 branches, where a 32-row unit holds 16 branches (each masked to its own suffix), and with a
     prefix shorter than one 64-key tile (no whole tile: every prefix key in the masked tail tiles)."""
@@ -226,22 +248,26 @@ def _scored(w, how):
     w.prefix_k[:] = W.bf16_bits(k)
 
 
+@pytest.mark.parametrize("d,blocks", [(128, 0), (128, 8), (64, 0), (64, 8)])
 @pytest.mark.parametrize("how", ["rising", "falling", "low-first", "high-first"])
-def test_prefill_tiled_moving_reference(fa, how):
+def test_prefill_tiled_moving_reference(fa, how, d, blocks):
     """The tiled kernel takes its exponentials against a row's old reference and moves it only when
     they have grown past a limit: scores that climb by hundreds along the keys (p overflows against
     the old reference), that fall (p underflows), and a first tile far below or above the rest; a
     prefix of whole tiles and 37 more keys, suffixes of 300-330 keys, whose tail tiles are shared by
-    all ranges.  Every row checked, contiguous and paged."""
+    all ranges.  By the plan's ranges (two or three whole tiles each) and with an explicit grid of one
+    range of 23, which goes through the loop unrolled over the four tile buffers (from seven tiles on).
+    Every row checked, contiguous and paged."""
     n = 60
-    w = W.make(W.CONFIGS["mid"].replace(n_kv_heads=2, n_q_heads=8, n_branches=4, prefix_len=1509,
+    w = W.make(W.CONFIGS["mid"].replace(head_dim=d, n_kv_heads=2, n_q_heads=8, n_branches=4, prefix_len=1509,
                                         suffix_range=(300, 330), steps=n, seed=2765))
     _scored(w, how)
     q, sk, sv = _instruction(w, n)
     ref, ref_lse = _reference(w, n, q, sk, sv)
-    plan, out, lse = _run(fa, w, n, q, sk, sv)
-    pplan, pout, plse = _run_paged(fa, w, n, q, sk, sv, seed=2766)
-    assert plan.info().units_per_block == 8 and plan.info().n_slots > 1
+    plan, out, lse = _run(fa, w, n, q, sk, sv, blocks=blocks)
+    pplan, pout, plse = _run_paged(fa, w, n, q, sk, sv, seed=2766, blocks=blocks)
+    for p in (plan, pplan):
+        assert p.info().units_per_block == 8 and (p.info().n_slots == 1) == (blocks > 0)
     for what, o, l in (("contiguous", out, lse), ("paged", pout, plse)):
         gates.assert_gates(o, ref, what=f"{how}, {what}")
         # lse up to 1000s here: fp32 roundings of the scores (2^-24 of |q||k| summed over d) and of lse
@@ -315,13 +341,14 @@ def test_prefill_tiled_explicit_grid(fa, blocks, ranges):
         assert plan.device_error() == 0
 
 
-def test_prefill_tiled_nonfinite_instruction_value(fa):
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_tiled_nonfinite_instruction_value(fa, d):
     """A NaN in the value of instruction token 17 of branch 1 (KV head 1) reaches exactly the rows
     that attend to it: branch 1's tokens 17.. on that KV head's query heads.  Its earlier tokens and
     every other branch and KV head stay exact (a row that does not read the key multiplies it by
     p = 0, which must not turn into NaN), contiguous and paged."""
     n, G, hkv = 40, 5, 2
-    spec = W.CONFIGS["mid"].replace(n_kv_heads=hkv, n_q_heads=hkv * G, n_branches=3, prefix_len=900,
+    spec = W.CONFIGS["mid"].replace(head_dim=d, n_kv_heads=hkv, n_q_heads=hkv * G, n_branches=3, prefix_len=900,
                                     suffix_range=(3, 30), steps=n, seed=2760)
     w = W.make(spec)
     q, sk, sv = _instruction(w, n)
@@ -414,8 +441,8 @@ def test_prefill_tiled_rows_do_not_depend_on_other_branches(fa, d, blocks, how):
 
 
 def test_prefill_paired_units_on_the_streaming_path(fa):
-    """Fewer than 256 rows per KV head keeps the partial kernel's prefill instantiation; with 64 KV
-    heads its items (5 units of 32 rows x 64) outnumber the resident blocks, so an eight-wave block
+    """Five units of 32 rows over 700 keys of 64 KV heads take the partial kernel's prefill instantiation;
+    its items (5 x 64) outnumber the resident blocks, so an eight-wave block
     takes two units of one KV head, four waves each.  Every row checked, contiguous and paged."""
     n = 30
     spec = W.CONFIGS["long"].replace(prefix_len=700, n_branches=5, n_kv_heads=64, n_q_heads=64,
@@ -596,11 +623,20 @@ def test_prefill_paged_random_shapes(fa, c):
     assert plan.device_error() == 0
 
 
-def test_prefill_paged_flags_a_bad_page(fa):
+# Shapes on either side of the kernel choice: (spec, tokens, tiled)
+_BOTH_KERNELS = [
+    (W.CONFIGS["tiny"], 4, True),
+    (W.CONFIGS["mid"].replace(head_dim=64, n_kv_heads=16, n_q_heads=16, n_branches=4, prefix_len=3751), 4, False),
+    (W.CONFIGS["mid"].replace(n_kv_heads=2, n_q_heads=10, n_branches=4, prefix_len=3000), 13, False),
+]
+_BOTH_IDS = ["tiled-d64", "streaming-d64", "streaming-d128"]
+
+
+@pytest.mark.parametrize("spec,n,tiled", _BOTH_KERNELS, ids=_BOTH_IDS)
+def test_prefill_paged_flags_a_bad_page(fa, spec, n, tiled):
     """A page id outside the pool in one branch's suffix row is not read (flag 4); the other
-    branches are exact."""
-    n = 4
-    w = W.make("tiny", steps=n, suffix_range=(10, 20), seed=2730)
+    branches are exact.  On both kernels."""
+    w = W.make(spec.replace(steps=n, suffix_range=(10, 20), seed=2730))
     q, sk, sv = _instruction(w, n)
     s = w.spec
     N, _, Hq, d = q.shape
@@ -608,6 +644,7 @@ def test_prefill_paged_flags_a_bad_page(fa):
     table[2, -(-w.prefix_len // 16)] = kp.shape[0] + 100
     plan = fa.Plan.prefill_paged_plan(s.n_q_heads, s.n_kv_heads, s.head_dim, N, n, w.prefix_len, table.shape[1],
                                       kp.shape[0], w.suffix_cap)
+    assert (plan.info().units_per_block == 8) == tiled
     out = torch.full((N, n, Hq, d), float("nan"), device="cuda")
     plan.prefill_paged(dev_bf16(q), dev_bf16(kp), dev_bf16(vp), dev_i32(table), dev_i32(w.suffix_len), out)
     torch.cuda.synchronize()
@@ -617,15 +654,17 @@ def test_prefill_paged_flags_a_bad_page(fa):
     gates.assert_gates(out.cpu().numpy().reshape(N * n, Hq, d)[rows], ref[rows], what="other branches exact")
 
 
-def test_prefill_clamps_and_flags_a_suffix_past_the_bound(fa):
-    """A suffix length above max_suffix_len - n is clamped to it (and flagged), like a decode's."""
-    n = 5
-    w = W.make("tiny", steps=n, suffix_range=(10, 20), seed=2602)
+@pytest.mark.parametrize("spec,n,tiled", _BOTH_KERNELS, ids=_BOTH_IDS)
+def test_prefill_clamps_and_flags_a_suffix_past_the_bound(fa, spec, n, tiled):
+    """A suffix length above max_suffix_len - n is clamped to it (and flagged), like a decode's.  On both
+    kernels."""
+    w = W.make(spec.replace(steps=n, suffix_range=(10, 20), seed=2602))
     q, sk, sv = _instruction(w, n)
     cap = w.suffix_cap
     bad = w.suffix_len.copy()
     bad[1] = cap + 3
     plan, out, lse = _run(fa, w, n, q, sk, sv, suffix_len=bad)
+    assert (plan.info().units_per_block == 8) == tiled
     assert plan.device_error() == 1
     # branch 1 now reads up to its clamped bound (the NaN past its data); the others are exact
     ref, ref_lse = _reference(w, n, q, sk, sv)
