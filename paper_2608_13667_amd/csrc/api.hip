@@ -505,8 +505,8 @@ struct PrefillLayout {
     int32_t n_pool_pages;
 };
 
-// Whether an instruction prefill of `rows` query rows per KV head over `keys` prefix keys (summed over
-// the KV heads) takes the tiled kernel or the partial kernel's prefill instantiation.  The tiled kernel
+// Whether an instruction prefill takes the tiled kernel or the partial kernel's prefill instantiation, by its units of
+// 32 query rows per KV head and its prefix keys summed over the KV heads.  The tiled kernel
 // takes 1.5-2 us for each of a block's steps of 64 keys, however few, and cuts the prefix into at most
 // 256 blocks; the instantiation spreads the smallest call over the whole device, but starts later (15 us
 // against 11) and loads every key again for each unit of 32 rows.  So the tiled kernel is ahead where
@@ -519,13 +519,33 @@ struct PrefillLayout {
 //   22.5 / 23.6, 2000 28.5 / 35.9, where the instantiation has no block left for a second range)
 //   d 64,  1 unit:  600 9.2 / 11.7, 8000 13.1 / 13.4, 14000 15.9 / 14.6; 2 units: 14000 17.4 / 18.9, 32768 26.0 / 23.2;
 //          8 units: 2000 19.2 / 19.0, 32768 41 / 65; 2 KV heads 8000 16.9 / 17.4, 14000 19.1 / 18.0, 32768 24.0 / 23.1
-bool use_prefill_tiles(int head_dim, int64_t rows, int64_t keys, int64_t n_kv_heads)
+//   d 128, 2 units, 8 KV heads: 12500 keys each 23.1 / 21.6, 16255 24.9 / 22.9 (4 KV heads 22500 20.9 / 24.3: twice the ranges)
+// A short prefix has few ranges, and where six or more units share a block's steps, with a tail group per branch at
+// least, the tail makes them four or five: d 128, 10 tokens x 5 branches (8 units) over 150 / 300 / 600 keys 19 / 19 / 18 against
+// 15 on the instantiation at 1-4 KV heads, 7 units 300 keys 17.6 / 15.4, 6 units 150 keys 19.6 / 14.6; 4 units of 5 branches 15000 keys in all 18.1 / 16.
+// The suffixes count too.  The instantiation scores them for each token by itself, the tiled kernel for 32 rows at
+// once, in tiles that one or two tokens leave nearly empty: one token of 8 branches over 2022 keys and suffixes of up to 2000
+// (8 KV heads, G 1) 18.6 / 12.9, 190 tokens of 2 branches over 1682 (suffixes up to 40) 25.8 / 51, 93 of 5 over 781 (up to 1000) 29.5 / 162.
+// The lengths are known on the device only: half of their room is taken for the first, all of it for the second, where the
+// tiled kernel is ahead by far or behind by little.
+bool use_prefill_tiles(const fka_plan *p)
 {
-    const int64_t units = ceil_div(rows, (int64_t)fka::prefill_tiles_unit_rows()), work = units * keys;
-    if (units == 1) return keys <= 60000;
-    if (units == 2) return head_dim == 128 || keys <= 120000;
+    const int64_t rows = (int64_t)p->n_seqs * p->G, n_kv_heads = p->Hkv, keys = p->prefix_len * n_kv_heads;
+    const int64_t units = ceil_div(rows, fka::prefill_tiles_unit_rows()), work = units * keys;
+    if (units <= 2) {
+        const int64_t room = p->prefill_n <= 2 ? (int64_t)p->n_branches * (p->max_suffix_len - p->prefill_n) / 2 * n_kv_heads : 0;
+        if (units == 1) return keys + room <= 60000;
+        if (p->d == 128) return keys + room <= 90000 || n_kv_heads < 8 || p->G > 32;
+        return keys + room <= 120000;
+    }
     if (units >= 28 || (units >= 8 && units * n_kv_heads >= 128)) return true;
-    if (head_dim == 64) return units < 7 || units * n_kv_heads > 60 || work <= 130000 || work >= 430000;
+    if (p->max_suffix_len >= 200 && (int64_t)p->n_seqs * n_kv_heads * p->max_suffix_len >= 320000) return true;
+    if (p->d == 64) return units < 7 || units * n_kv_heads > 60 || work <= 130000 || work >= 430000;
+    if (units <= 8 && p->G <= 32) {
+        if (units == 4 && p->n_branches > 1) return work <= 48000 || work >= 190000;
+        if (units >= 6 && keys <= 330 * n_kv_heads && (p->n_branches >= 3 || (units >= 7 && n_kv_heads <= 4))) return false;
+        if (units == 8 && p->n_branches >= 3) return work >= 270000;
+    }
     if (units <= 4) return work <= 60000 || work >= 190000;
     return work <= (units <= 8 ? 20000 : 45000) || work >= 270000;
 }
@@ -571,7 +591,7 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device)) != hipSuccess)
         return bail(hip_fail(e, "hipDeviceGetAttribute"));
     const int tile_rows = fka::prefill_tiles_unit_rows(), tile_waves = fka::prefill_tiles_waves();
-    if (use_prefill_tiles(p->d, S * G, (int64_t)Lp * p->Hkv, p->Hkv)) {
+    if (use_prefill_tiles(p)) {
         // The tiled kernel: units of 32 consecutive rows of a KV head, eight per block (one per
         // wave) over one of R ranges of the keys, R such that the blocks fill the device.
         const int per_cu = fka::prefill_tiles_blocks_per_cu(p->d, lay.paged);

@@ -281,6 +281,17 @@ def test_prefill_tiled_moving_reference(fa, how, d, blocks):
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=3750), True),   # 60000 keys
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=4, n=8, prefix_len=3751), False),
     (dict(head_dim=128, n_kv_heads=8, n_q_heads=8, n_branches=3, n=11, prefix_len=700), True),     # 2 units
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=8, n_branches=3, n=11, prefix_len=11250), True),   # ... 90000 keys, 8 KV heads
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=8, n_branches=3, n=11, prefix_len=11251), False),
+    (dict(head_dim=128, n_kv_heads=4, n_q_heads=4, n_branches=3, n=11, prefix_len=22600), True),   # ... 4 KV heads
+    (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=5, n=5, prefix_len=6000), True),    # 4 units, 12000 keys
+    (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=5, n=5, prefix_len=6001), False),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=6, n=6, prefix_len=330), False),    # 6 units, several branches
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=6, n=6, prefix_len=331), True),
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=2, n=18, prefix_len=300), True),    # ... two branches
+    (dict(head_dim=128, n_kv_heads=4, n_q_heads=20, n_branches=1, n=43, prefix_len=200), False),   # 7 units, 4 KV heads
+    (dict(head_dim=128, n_kv_heads=8, n_q_heads=40, n_branches=1, n=43, prefix_len=200), True),    # ... 8 KV heads
+    (dict(head_dim=128, n_kv_heads=2, n_q_heads=10, n_branches=5, n=10, prefix_len=600), False),   # 8 units, several branches
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=1250), True),  # 3 units, 20000 keys
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=1251), False),
     (dict(head_dim=128, n_kv_heads=16, n_q_heads=16, n_branches=5, n=13, prefix_len=3958), False),
