@@ -322,8 +322,8 @@ fka_status fka_scatter_pages(const void *k_src, const void *v_src, int32_t len, 
  * is dominated by prefill over the cached prefix).  Every branch b takes n_tokens instruction
  * tokens at once: token t's queries attend to the whole shared prefix and, causally, to b's
  * suffix up to and including its own position (suffix positions [0, suffix_len[b] + t]).
- * The plan takes one of two kernels, by the query rows (N x n_tokens x G) per KV head and the prefix
- * keys.  The tiled kernel: each KV head's rows are cut into units of 32 consecutive rows, a block of
+ * The plan takes one of two kernels, by the query rows (N x n_tokens x G) per KV head, the prefix
+ * keys and the suffixes' bound.  The tiled kernel: each KV head's rows are cut into units of 32 consecutive rows, a block of
  * eight waves takes up to eight units (one each) over one range of 64-key tiles, which it loads once
  * into LDS for all of them, and the blocks of one KV head run on one XCD (the KV head varies
  * fastest in the grid) so that its ranges come from HBM once; the prefix's last prefix_len mod 64

@@ -25,10 +25,10 @@ struct fka_plan {
     int32_t prefill_groups = 1; // instruction prefill plan: units per block
     int32_t set_blocks = 1;     // ... blocks per set of units
     fka::ExactDiv by_prefill_n{}, by_sets{}, by_kv_heads{};
-    // instruction prefill on the tiled kernel: 32-row units per KV head, blocks of
-    // eight units, key ranges, whole prefix tiles of 64 keys
+    // instruction prefill on the tiled kernel: blocks of up to eight 32-row units, key ranges (all,
+    // those with prefix tiles), whole prefix tiles of 64 keys
     bool prefill_tiles = false;
-    int32_t tile_units = 0, tile_unit_groups = 0, tile_ranges = 0, tile_prefix_ranges = 0, tile_prefix = 0;
+    int32_t tile_unit_groups = 0, tile_ranges = 0, tile_prefix_ranges = 0, tile_prefix = 0;
     fka::TileSplit tile_split{};
     int32_t max_suffix_len = 0;
     // contiguous
@@ -440,7 +440,6 @@ fka_status run_prefill(const fka_plan *p, const fka::AttnArgs &a, float *out, fl
         t.n_q_heads = p->Hq;
         t.n_kv_heads = p->Hkv;
         t.group = p->G;
-        t.n_units = p->tile_units;
         t.unit_groups = p->tile_unit_groups;
         t.ranges = p->tile_ranges;
         t.prefix_ranges = p->tile_prefix_ranges;
@@ -633,7 +632,6 @@ fka_status create_prefill(const fka_heads *heads, int32_t N, int32_t n, int32_t 
         R = std::max<int64_t>(1, std::min<int64_t>(R, ((int64_t)256 << 20) / range_bytes));
         RP = std::min(R, RP);
         p->prefill_tiles = true;
-        p->tile_units = U;
         p->tile_unit_groups = UG;
         p->tile_ranges = (int32_t)R;
         p->tile_prefix_ranges = (int32_t)RP;

@@ -332,11 +332,11 @@ struct ScatterArgs {
 // Instruction prefill as a tiled multi-query kernel (prefill.hip).  Rows of KV head g
 // are cut into units of 32 (row i: query head g G + i mod G of virtual sequence i / G, where
 // sequence s = b n + t is instruction token t of branch b); block vb takes KV head vb mod Hkv,
-// unit group k = (vb / Hkv) mod unit_groups (units [floor(k U / UG), floor((k + 1) U / UG)), at
-// most eight, one per wave) and range r = vb / (Hkv unit_groups) of `ranges`: of the T tiles of 64
-// keys its rows read -- the prefix's whole tiles, then its last Lp mod 64 keys and the suffix keys
-// in groups of eight, counted on the device from the suffix lengths -- those in [floor(r T / R),
-// floor((r + 1) T / R)).  Part r of output row (s, h) is written at
+// unit group (vb / Hkv) mod unit_groups (units / unit_groups consecutive units, the first groups one
+// more where there is a remainder; at most eight, one per wave) and range r = vb / (Hkv unit_groups)
+// of `ranges`.  The first prefix_ranges of these have the prefix's whole 64-key tiles, as many each, the first
+// ones one more; the prefix's last Lp mod 64 keys and the suffix keys form tail tiles of eight 8-key groups,
+// counted on the device from the suffix lengths and dealt by tail_share.  Part r of output row (s, h) is written at
 // part_o[(r S Hq + s Hq + h) d] and part_lse[r S Hq + s Hq + h].
 struct PrefillArgs {
     const uint16_t *q;                    // [S][Hq][d]
@@ -353,8 +353,7 @@ struct PrefillArgs {
     int32_t max_pages, n_pool_pages;
     int32_t paged;
     int32_t n_q_heads, n_kv_heads, group;
-    int32_t n_units;       // 32-row units per KV head
-    int32_t unit_groups;   // ceil(n_units / 8)
+    int32_t unit_groups;   // ceil(units / 8)
     int32_t ranges;        // R
     int32_t prefix_ranges; // of these, the first that have the prefix's whole tiles
     int32_t prefix_tiles;  // floor(Lp / 64): whole 64-key tiles

@@ -40,8 +40,9 @@
 // What bounds it: beside a wave that issues matrix products at full rate the other wave of the SIMD
 // gets one vector issue per 8.7 cycles (two per product), so a step cannot be shorter than 2 x 96
 // products (3340 cycles) nor than the two softmaxes' ~225 issue slots each (3900); it takes 3940
-// (124 steps, 32k prefix, 64 tokens x 5 branches, 40 / 8 heads), where the chip's power limit holds
-// the clock at 2.2 of 2.4 GHz.  With the operands read in bursts that were waited for whole, a
+// (32k prefix, 64 tokens x 5 branches, 40 / 8 heads), where the chip's power limit holds
+// the clock at 2.2 of 2.4 GHz: 1.79 us, or 229 of the kernel's 260 us for the 128 tiles of a range (the rest: the start, the tail, the
+// partials' stores at the end).  With the operands read in bursts that were waited for whole, a
 // maximum per tile and the keys past the whole tiles read wave by wave, one round trip to memory per
 // 32 keys (25000 cycles in the last range), it took 4920: 292 us a call against 265 now, 235
 // against 211 at 256 tokens x 1 sequence over 33.8k keys, 74.5 against 65.5 at 16 x 5 over 23k.  (The sums

@@ -1,7 +1,8 @@
 // Host-side check of the reciprocal forms that a static split of whole blocks uses in place of the
 // general split's divisions (internal.h): div_magic against x / d, and even_split against pre_split and
 // suf_split for every worker, over random sizes up to the bounds they are used within (W <= 1024,
-// slices x W < 2^31) and the small ones exhaustively; ExactDiv over all dividends and divisors.  Prints "ok <cases>" or the first failure.
+// slices x W < 2^31) and the small ones exhaustively; ExactDiv, whose
+// bound stands at its definition, on both sides of quotients of some 200000 divisors.  Prints "ok <cases>" or the first failure.
 #include <cstdio>
 #include <cstdlib>
 #include <random>
