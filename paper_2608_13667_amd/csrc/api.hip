@@ -507,17 +507,17 @@ struct PrefillLayout {
 // Whether an instruction prefill takes the tiled kernel or the partial kernel's prefill instantiation, by its units of
 // 32 query rows per KV head and its prefix keys summed over the KV heads.  The tiled kernel
 // takes 1.5-2 us for each of a block's steps of 64 keys, however few, and cuts the prefix into at most
-// 256 blocks; the instantiation spreads the smallest call over the whole device, but starts later (15 us
+// 256 blocks; the instantiation spreads the smallest call over the whole device, but starts later (14 us
 // against 11) and loads every key again for each unit of 32 rows.  So the tiled kernel is ahead where
 // two steps are enough and where the products count, and behind in between.  Measured, us tiled /
 // instantiation, 8 KV heads where nothing else is said:
-//   d 128, 1 unit:  600 keys 10.6 / 14.4, 8000 17.0 / 17.2, 14000 21.0 / 20.3, 32768 36.1 / 32.5
-//          3 units: 600 12.5 / 14.9, 3500 17.7 / 16.1, 8000 20.9 / 21.4, 14000 25.6 / 27.3
-//          8 units: 300 18.6 / 18.0, 2000 25.5 / 21.0, 3500 27.9 / 26.0, 5000 27.8 / 30.5, 32768 61 / 120
+//   d 128, 1 unit:  600 keys 10.7 / 13.8, 8000 15.1 / 14.8, 14000 20.7 / 19.3, 32768 33.2 / 28.1
+//          3 units: 600 12.7 / 15.1, 3500 17.0 / 16.3, 8000 19.7 / 20.6, 14000 24.4 / 25.9
+//          8 units: 300 20.5 / 17.7, 2000 25.6 / 21.6, 3500 28.0 / 25.8, 5000 28.1 / 30.3, 32768 58 / 111
 //   (2 and 4 KV heads cross at about the same products units x keys; 19 units of 8 KV heads, 600 keys
-//   22.5 / 23.6, 2000 28.5 / 35.9, where the instantiation has no block left for a second range)
-//   d 64,  1 unit:  600 9.2 / 11.7, 8000 13.1 / 13.4, 14000 15.9 / 14.6; 2 units: 14000 17.4 / 18.9, 32768 26.0 / 23.2;
-//          8 units: 2000 19.2 / 19.0, 32768 41 / 65; 2 KV heads 8000 16.9 / 17.4, 14000 19.1 / 18.0, 32768 24.0 / 23.1
+//   23.0 / 26.2, 2000 29.5 / 38.0, where the instantiation has no block left for a second range)
+//   d 64,  1 unit:  600 9.2 / 11.4, 8000 12.0 / 11.8, 14000 15.1 / 12.7; 2 units: 14000 16.9 / 18.4, 32768 26.1 / 23.2;
+//          8 units: 2000 19.1 / 19.2, 32768 41 / 64; 2 KV heads 8000 17.2 / 16.6, 14000 19.9 / 18.5, 23017 22.7 / 22.7, 32768 24.7 / 25.8
 //   d 128, 2 units, 8 KV heads: 12500 keys each 23.1 / 21.6, 16255 24.9 / 22.9 (4 KV heads 22500 20.9 / 24.3: twice the ranges)
 // A short prefix has few ranges, and where six or more units share a block's steps, with a tail group per branch at
 // least, the tail makes them four or five: d 128, 10 tokens x 5 branches (8 units) over 150 / 300 / 600 keys 19 / 19 / 18 against
